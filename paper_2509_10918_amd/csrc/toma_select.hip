@@ -12,6 +12,7 @@
 //   k_greedy  one workgroup per (sample, region); the region's whole S (up to 256 x 256 words)
 //             lives in the workgroup's vector registers and the rows' values are kept up to date
 //             incrementally (see the comment at the kernel).
+#include <algorithm>
 #include <type_traits>
 
 #include "toma_common.h"
@@ -196,6 +197,20 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
   const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
   return max(max(a, b), max(c, d));
+}
+// the same over lanes 0 .. 31
+__device__ __forceinline__ uint32_t half_max_u32(uint32_t v) {
+  v = max(v, dpp_u32<kDppXor1>(v));
+  v = max(v, dpp_u32<kDppXor2>(v));
+  v = max(v, dpp_u32<kDppRor4>(v));
+  v = max(v, dpp_u32<kDppRor8>(v));
+  return max((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+}
+__device__ __forceinline__ uint64_t half_max_u64(uint64_t k) {
+  const uint32_t hi = (uint32_t)(k >> 32), lo = (uint32_t)k;
+  const uint32_t top_hi = half_max_u32(hi);
+  const uint32_t top_lo = half_max_u32(hi == top_hi ? lo : 0u);
+  return ((uint64_t)top_hi << 32) | top_lo;
 }
 // max over the 64 lanes of 64-bit keys: the largest high word, then the largest low word among its
 // holders; the result is uniform
@@ -536,131 +551,401 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
 // ------------------------------------------------------------------------------------------------
 // The same greedy selection for regions too large for one CU's registers (more than 256 tokens, up to
 // kBigRegion: the few-regions end of the paper's region-count ablation, e.g. four regions of 1024
-// tokens).  One workgroup of 1024 threads per (sample, region); S stays in global memory (it is read
-// through L2), thread i owns row i and column i (and i + 1024): its row's value as a 64-bit integer and
-// its column's coverage live in registers.  A round: (1) argmax of the keys - value + 1 in the high
-// bits, 4095 - row in the low twelve, so the largest key is the largest value at the lowest row - by
-// a wave reduction, an exchange through LDS and a second wave reduction that every wave does for
-// itself; (2) every thread compares row t (one coalesced read) with its columns' coverage and appends
-// the changed columns (column, old, new coverage) to a list in LDS; (3) every thread walks the list and
-// lowers its rows' values by med(S_ij, m_j, m_j') - m_j, reading S_ji = S_ij along row j (coalesced).
-// Integer arithmetic throughout: the values equal the full rescan of Alg. 2 whatever the order of the
-// list.  Three barriers per round.
-constexpr int kBigRegion = 2048, kBigThreads = 1024, kBigRows = kBigRegion / kBigThreads;
+// tokens).  One workgroup per (sample, region); S stays in global memory (it is read through L2), a
+// thread owns one row and column (two past 1024 tokens): its row's value as a 64-bit integer and its
+// column's coverage live in registers.
+//
+// What bounds it is the chain of a round - argmax, row t from L2, the changed columns' rows of S from L2 -
+// on the one CU of the region, so a round takes SEVERAL picks wherever that cannot change the result:
+//   (1) candidates: all rows whose key (value + 1 in the high bits, 4095 - row in the low twelve) reaches
+//       the threshold T, the kCandRank-th largest of the 16-lane groups' largest keys; every other key is
+//       below T, and keys never grow.
+//   (2) every thread compares the candidates' rows with its columns' coverage m.  A column j where
+//       several candidates exceed m_j lowers one's value when the other is picked, by
+//       min(S_pj, S_qj) - m_j; these pair terms are added up exactly in LDS.
+//   (3) one wave replays the greedy rule on the candidates: the largest current key is the next pick
+//       while it is >= T and no pick of this round has touched its value (then the changed columns of the
+//       round's picks are disjoint, so the pair terms, taken at the round's start, stay exact); the
+//       others' keys fall by their pair terms.  It stops at the first that does not qualify.
+//   (4) the changed columns of all picks go into one list, and every thread lowers its rows' values by
+//       med(S_ij, m_j, m_j') - m_j over the list, reading S_ji = S_ij along row j (coalesced).
+// The first rounds, in which a pick changes most columns, the rounds whose candidates crowd one column
+// and the variant that records gaps take the top candidate alone.  Integer arithmetic throughout: picks
+// and values equal the full rescan of Alg. 2.
+// 8 regions of 1024 tokens, 512 picks each: 1846 us with one pick per round, 980 us with this and k_big_round.
+// (A batch's loads are requested unguarded, with clamped indices, before the first is used: with a guard around
+// each the compiler waits for every load by itself, which alone costs 450 us.)
+constexpr int kBigRegion = 2048, kBigThreads = 1024;
+constexpr int kCandMax = 32;    // candidate slots of a round
+constexpr int kCandRank = 12, kCandRankDense = 6;  // group maxima that reach the threshold
+constexpr int kCandHeld = 8;    // candidates that may exceed one column's coverage
+// changed columns per pick up to which rounds take several picks, and up to which they take them from the longer list
+constexpr int kSparse = 64, kSparser = 12;
 
-__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) { return wave_max_u64(k); }
+// State of the selection of one large region between kernels: keys (0 = picked), coverage, picks so far.
+struct BigState { uint64_t *key; int32_t *m; uint64_t *pick; };
 
-template <bool GAP>
+// One of the first rounds of a large region, as a launch of its own over the whole chip: these rounds change
+// hundreds of columns per pick and would have the region's one CU stream most of S.  A workgroup takes 16 rows;
+// all workgroups of a region find the same pick, raise the same coverage, and each lowers its own rows' values.
+// FIRST: no pick, the rows' values under the starting coverage.  The state is double-buffered (in -> out).
+// 8 regions of 1024 tokens: 10 us per launch, where the single workgroup took 200 us for the first values and
+// 33 us per pick for the next seven; from about the eighth pick on it is the faster one (7 us, 4 us after the 32nd).
+constexpr int kBigFirst = 128;
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_big_round(const int32_t *__restrict__ S, BigState in, BigState out, int n, int step) {
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  constexpr int32_t kFloor = -(1 << 30);
+  __shared__ __align__(16) int32_t lo[kBigRegion], hi[kBigRegion];  // coverage before and after the pick
+  __shared__ uint64_t red[4];
+  const int blocks = n / 16, bp = blockIdx.x / blocks, blk = blockIdx.x % blocks;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int32_t *Sr = S + (size_t)bp * n * n;
+  const size_t at = (size_t)bp * n;
+  int t = -1;
+  if constexpr (!FIRST) {
+    uint64_t best = 0;
+    for (int i = tid; i < n; i += 256) {
+      const uint64_t k = in.key[at + i];
+      best = k > best ? k : best;
+    }
+    best = wave_max_u64(best);
+    if (lane == 0) red[w] = best;
+    __syncthreads();
+    const uint64_t top = wave_max_u64(red[lane & 3]);
+    t = 4095 - (int)(top & 4095);
+    if (blk == 0 && tid == 0) out.pick[at + step] = top;
+    for (int j = tid; j < n; j += 256) {
+      const int32_t a = in.m[at + j], b = max(a, Sr[(size_t)t * n + j]);
+      lo[j] = a;
+      hi[j] = b;
+      if (blk == 0) out.m[at + j] = b;
+    }
+    __syncthreads();
+  } else {
+    if (blk == 0)
+      for (int j = tid; j < n; j += 256) out.m[at + j] = kFloor;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int row = 16 * blk + 4 * w + r;
+    uint64_t sum = 0;
+    for (int j = 4 * lane; j < n; j += 256) {
+      if constexpr (FIRST) {
+        const i32x4 s = *reinterpret_cast<const i32x4 *>(Sr + (size_t)row * n + j);
+#pragma unroll
+        for (int u = 0; u < 4; u++) sum += (uint32_t)(s[u] - kFloor);
+      } else {
+        const i32x4 a = *reinterpret_cast<const i32x4 *>(lo + j), b = *reinterpret_cast<const i32x4 *>(hi + j);
+        if (a[0] != b[0] || a[1] != b[1] || a[2] != b[2] || a[3] != b[3]) {
+          const i32x4 s = *reinterpret_cast<const i32x4 *>(Sr + (size_t)row * n + j);
+#pragma unroll
+          for (int u = 0; u < 4; u++) sum += (uint32_t)(min(max(s[u], a[u]), b[u]) - a[u]);
+        }
+      }
+    }
+#pragma unroll
+    for (int msk = 1; msk < 64; msk <<= 1) sum += __shfl_xor((unsigned long long)sum, msk, 64);
+    if (lane == 0) {
+      if constexpr (FIRST) {
+        out.key[at + row] = ((sum + 1) << 12) | (uint64_t)(4095 - row);
+      } else {
+        const uint64_t k = in.key[at + row];
+        out.key[at + row] = row == t || k == 0 ? 0ull : k - (sum << 12);
+      }
+    }
+  }
+}
+
+template <int ROWS, bool GAP>
 __global__ __launch_bounds__(kBigThreads) void k_greedy_big(const int32_t *__restrict__ S, int32_t *__restrict__ idx,
                                                            float *__restrict__ gain_out, float *__restrict__ gap_out,
-                                                           RegionMap map, int P, int n, int d_loc) {
+                                                           RegionMap map, int P, int n, int d_loc,
+                                                           BigState init, int step0) {
   constexpr int32_t kFloor = -(1 << 30);  // similarity -1: the coverage before the first pick
-  constexpr int NW = kBigThreads / 64;
-  __shared__ uint64_t red[NW], red2[GAP ? NW : 1];
-  __shared__ int list_n;
-  __shared__ int32_t list_j[kBigRegion], list_a[kBigRegion], list_b[kBigRegion];
-  const int bp = blockIdx.x, p = bp % P, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  constexpr int NMAX = kBigThreads * ROWS;
+  __shared__ uint64_t group_top[kBigThreads / 16];           // largest key of every 16 lanes
+  __shared__ uint64_t dec_pair[GAP ? 1 : kCandMax * kCandMax];  // pair terms, at [smaller slot][larger slot]
+  __shared__ uint64_t cand_key[kCandMax], threshold;
+  __shared__ uint64_t pick_key[NMAX];
+  __shared__ float pick_gap[GAP ? NMAX : 1];
+  __shared__ uint64_t red2[GAP ? kBigThreads / 64 : 1];
+  __shared__ int list_n, cand_n, crowded, picks_n;
+  __shared__ uint32_t picks_mask;
+  __shared__ int32_t list_j[NMAX], list_a[NMAX], list_b[NMAX];
+  const int bp = blockIdx.x, p = bp % P, tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), groups = nthr / 16;
   const int32_t *Sr = S + (size_t)bp * n * n;
+  // (only LDS passes between threads: the barriers need not wait for global loads)
+  auto lds_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
-  int row[kBigRows];
-  bool live[kBigRows], picked[kBigRows];
-  int32_t m[kBigRows];
-  uint64_t val[kBigRows];
+  int row[ROWS];
+  bool live[ROWS], picked[ROWS];
+  int32_t m[ROWS];
+  uint64_t val[ROWS];
 #pragma unroll
-  for (int u = 0; u < kBigRows; u++) {
-    row[u] = tid + kBigThreads * u;
+  for (int u = 0; u < ROWS; u++) {
+    row[u] = tid + nthr * u;
     live[u] = row[u] < n;
-    picked[u] = false;
+    row[u] = live[u] ? row[u] : n - 1;  // (a thread without a row reads the last one's words and drops them)
+    picked[u] = !live[u];
     m[u] = kFloor;
     val[u] = 0;
   }
-  if (tid == 0) list_n = 0;
-  // values under the starting coverage: sum_j (S_ij + 1), summed down the columns (S is symmetric)
-  for (int j = 0; j < n; j++) {
+  if (tid == 0) { list_n = 0; cand_n = 0; crowded = 0; threshold = 1; }
+  if (init.key) {  // the first step0 picks were made by k_big_round
 #pragma unroll
-    for (int u = 0; u < kBigRows; u++)
-      if (live[u]) val[u] += (uint32_t)(Sr[(size_t)j * n + row[u]] - kFloor);
+    for (int u = 0; u < ROWS; u++) {
+      const uint64_t k = live[u] ? init.key[(size_t)bp * n + row[u]] : 0ull;
+      picked[u] = k == 0;
+      val[u] = k == 0 ? 0ull : (k >> 12) - 1;
+      m[u] = init.m[(size_t)bp * n + row[u]];
+    }
+    for (int k = tid; k < step0; k += nthr) pick_key[k] = init.pick[(size_t)bp * n + k];
+  } else {  // values under the starting coverage: sum_j (S_ij + 1), summed down the columns (S is symmetric)
+    int j = 0;
+    for (; j + 16 <= n; j += 16) {
+      int32_t x[16][ROWS];
+#pragma unroll
+      for (int q = 0; q < 16; q++)
+#pragma unroll
+        for (int u = 0; u < ROWS; u++) x[q][u] = Sr[(uint32_t)(j + q) * n + row[u]];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 16; q++)
+#pragma unroll
+        for (int u = 0; u < ROWS; u++) val[u] += (uint32_t)(x[q][u] - kFloor);
+    }
+    for (; j < n; j++)
+#pragma unroll
+      for (int u = 0; u < ROWS; u++) val[u] += (uint32_t)(Sr[(size_t)j * n + row[u]] - kFloor);
   }
 
-  for (int step = 0; step < d_loc; step++) {
-    // ---- (1) argmax ----
-    uint64_t best = 0, key[kBigRows];
+  bool sparse = step0 > 0;  // uniform: the previous round's picks changed few columns each
+  int want = kCandRankDense;
+  for (int step = step0; step < d_loc;) {
+    // ---- (1) the largest key of every 16 lanes, of all, and the threshold ----
+    uint64_t best = 0, key[ROWS];
 #pragma unroll
-    for (int u = 0; u < kBigRows; u++) {
-      key[u] = live[u] && !picked[u] ? ((val[u] + 1) << 12) | (uint64_t)(4095 - row[u]) : 0ull;
+    for (int u = 0; u < ROWS; u++) {
+      key[u] = picked[u] ? 0ull : ((val[u] + 1) << 12) | (uint64_t)(4095 - row[u]);
       best = key[u] > best ? key[u] : best;
     }
-    const uint64_t wbest = wave_max_key(best);
-    if (lane == 0) red[w] = wbest;
-    __syncthreads();
-    const uint64_t top = wave_max_key(lane < NW ? red[lane] : 0ull);
-    const int t = 4095 - (int)(top & 4095);
-    if constexpr (GAP) {
-      uint64_t sb = 0;
-#pragma unroll
-      for (int u = 0; u < kBigRows; u++) {
-        const uint64_t k = row[u] == t ? 0ull : key[u];
-        sb = k > sb ? k : sb;
-      }
-      const uint64_t wsb = wave_max_key(sb);
-      if (lane == 0) red2[w] = wsb;
+    {
+      uint32_t hi = (uint32_t)(best >> 32), lo = (uint32_t)best;
+      uint32_t top_hi = max(hi, dpp_u32<kDppXor1>(hi));
+      top_hi = max(top_hi, dpp_u32<kDppXor2>(top_hi));
+      top_hi = max(top_hi, dpp_u32<kDppRor4>(top_hi));
+      top_hi = max(top_hi, dpp_u32<kDppRor8>(top_hi));
+      lo = hi == top_hi ? lo : 0u;
+      lo = max(lo, dpp_u32<kDppXor1>(lo));
+      lo = max(lo, dpp_u32<kDppXor2>(lo));
+      lo = max(lo, dpp_u32<kDppRor4>(lo));
+      lo = max(lo, dpp_u32<kDppRor8>(lo));
+      if ((lane & 15) == 0) group_top[tid >> 4] = ((uint64_t)top_hi << 32) | lo;
     }
-    // ---- (2) row t against the coverage of the own columns ----
+    if constexpr (!GAP)
+      if (sparse)
+        for (int e = tid; e < kCandMax * kCandMax; e += nthr) dec_pair[e] = 0;
+    lds_barrier();
+    const uint64_t gk = lane < groups ? group_top[lane] : 0ull;
+    const uint64_t top = wave_max_u64(gk);
+    bool single = true;
+    uint32_t mine[ROWS];  // this thread's rows among the round's picks (slot bit)
 #pragma unroll
-    for (int u = 0; u < kBigRows; u++) {
-      if (!live[u]) continue;
-      const int32_t x = Sr[(size_t)t * n + row[u]];
-      if (x > m[u]) {
-        const int at = atomicAdd(&list_n, 1);
-        list_j[at] = row[u];
-        list_a[at] = m[u];
-        list_b[at] = x;
-        m[u] = x;
-      }
-      if (row[u] == t) picked[u] = true;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      const size_t at = (size_t)bp * d_loc + step;
-      idx[at] = map.token(p, t);
-      const uint64_t value = (top >> 12) - 1;
-      const double shown = (double)value - (step == 0 ? (double)n * kSimScale : 0.0);  // the first value is the row sum
-      if (gain_out) gain_out[at] = (float)(shown / kSimScale);
-      if constexpr (GAP) {
-        uint64_t second = 0;
-        for (int q = 0; q < NW; q++) second = red2[q] > second ? red2[q] : second;
-        gap_out[at] = second ? (float)((double)((top >> 12) - (second >> 12)) / kSimScale) : __builtin_inff();
-      }
-    }
-    // ---- (3) the changed columns lower the rows' values ----
-    constexpr int kBatch = 4;  // list entries (rows of S) whose loads are in flight together (a round seldom has more)
-    const int cnt = list_n;
-    uint64_t dec[kBigRows];
+    for (int u = 0; u < ROWS; u++) mine[u] = 0;
+    int taken = 1;
+
+    if constexpr (!GAP) {
+      if (sparse) {
+        // wave w ranks the maxima of its own four groups (keys are unique unless zero)
 #pragma unroll
-    for (int u = 0; u < kBigRows; u++) dec[u] = 0;
-    for (int e0 = 0; e0 < cnt; e0 += kBatch) {
-      int32_t sj[kBatch][kBigRows], a[kBatch], b[kBatch];
-#pragma unroll
-      for (int q = 0; q < kBatch; q++) {
-        const int e = min(e0 + q, cnt - 1);
-        const int j = list_j[e];
-        a[q] = list_a[e];
-        b[q] = e0 + q < cnt ? list_b[e] : a[q];  // (a repeated entry with a == b adds nothing)
-#pragma unroll
-        for (int u = 0; u < kBigRows; u++) sj[q][u] = live[u] ? Sr[(size_t)j * n + row[u]] : 0;
-      }
-#pragma unroll
-      for (int q = 0; q < kBatch; q++)
-#pragma unroll
-        for (int u = 0; u < kBigRows; u++) {
-          const int32_t cl3 = min(max(sj[q][u], a[q]), b[q]);  // a <= b
-          dec[u] += (uint32_t)(cl3 - a[q]);
+        for (int i = 0; i < 4; i++) {
+          const uint32_t vh = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(gk >> 32), 4 * w + i);
+          const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)gk, 4 * w + i);
+          const uint64_t v = ((uint64_t)vh << 32) | vl;
+          const int rank = __builtin_popcountll(__ballot(gk > v));
+          if (v != 0 && rank == want - 1 && lane == 0) threshold = v;
         }
-    }
+        lds_barrier();
+        const uint64_t T = threshold;
 #pragma unroll
-    for (int u = 0; u < kBigRows; u++) val[u] -= dec[u];
-    __syncthreads();  // everyone has read the list (and red / red2)
-    if (tid == 0) list_n = 0;
+        for (int u = 0; u < ROWS; u++)
+          if (key[u] >= T) {
+            const int at = atomicAdd(&cand_n, 1);
+            if (at < kCandMax) { cand_key[at] = key[u]; mine[u] = 1u << at; }
+          }
+        lds_barrier();
+        const int nc = __builtin_amdgcn_readfirstlane(cand_n);
+        if (nc <= kCandMax) {  // (uniform)
+          // ---- (2) the candidates' rows against the coverage of the own columns ----
+          int32_t held_x[kCandHeld][ROWS];
+          uint32_t held_k[kCandHeld][ROWS], held[ROWS];
+#pragma unroll
+          for (int u = 0; u < ROWS; u++) held[u] = 0;
+          constexpr int kRowsBatch = 16 / ROWS;
+          for (int k0 = 0; k0 < nc; k0 += kRowsBatch) {
+            int32_t x[kRowsBatch][ROWS];
+#pragma unroll
+            for (int q = 0; q < kRowsBatch; q++) {
+              const int k = min(k0 + q, nc - 1);
+              const int32_t *St = Sr + (uint32_t)(4095 - __builtin_amdgcn_readfirstlane((int)((uint32_t)cand_key[k] & 4095u))) * n;
+#pragma unroll
+              for (int u = 0; u < ROWS; u++) x[q][u] = St[row[u]];
+            }
+            __builtin_amdgcn_sched_barrier(0);  // (all requested before the first is looked at)
+#pragma unroll
+            for (int q = 0; q < kRowsBatch; q++)
+#pragma unroll
+              for (int u = 0; u < ROWS; u++)
+                if (k0 + q < nc && live[u] && x[q][u] > m[u]) {
+                  const uint32_t k = (uint32_t)(k0 + q);
+#pragma unroll
+                  for (int e = 0; e < kCandHeld; e++)
+                    if (e < (int)held[u])
+                      atomicAdd((unsigned long long *)&dec_pair[held_k[e][u] * kCandMax + k],
+                                (unsigned long long)(uint32_t)(min(held_x[e][u], x[q][u]) - m[u]));
+                  if (held[u] == kCandHeld) crowded = 1;
+#pragma unroll
+                  for (int e = 0; e < kCandHeld; e++)
+                    if (e == (int)held[u]) { held_x[e][u] = x[q][u]; held_k[e][u] = k; }
+                  held[u] = min(held[u] + 1u, (uint32_t)kCandHeld);
+                }
+          }
+          lds_barrier();
+          if (!crowded) {  // (uniform: written before the barrier, reset after the next two)
+            // ---- (3) the greedy rule on the candidates ----
+            if (w == 0) {
+              const uint64_t base = lane < nc ? cand_key[lane] : 0ull;
+              uint64_t cur = base;
+              uint32_t mask = 0;
+              int done = 0;
+              while (step + done < d_loc) {
+                const uint64_t t = half_max_u64(cur);
+                const int l = __builtin_ctzll(__ballot(cur == t));
+                // (the first is the top of all keys; a zero key ends it: T >= 1)
+                if (done && (t < T || ((__ballot(cur != base && cur != 0) >> l) & 1))) break;
+                if (lane == 0) pick_key[step + done] = t;
+                mask |= 1u << l;
+                done++;
+                const int lo = min(lane & (kCandMax - 1), l), hi = max(lane & (kCandMax - 1), l);
+                const uint64_t d = dec_pair[lo * kCandMax + hi];
+                cur = lane == l || cur == 0 ? 0ull : cur - (d << 12);
+              }
+              if (lane == 0) { picks_mask = mask; picks_n = done; }
+            }
+            lds_barrier();
+            const uint32_t mask = picks_mask;
+            taken = __builtin_amdgcn_readfirstlane(picks_n);
+            // ---- the changed columns: each by one pick ----
+#pragma unroll
+            for (int u = 0; u < ROWS; u++) {
+#pragma unroll
+              for (int e = 0; e < kCandHeld; e++)
+                if (e < (int)held[u] && ((mask >> held_k[e][u]) & 1u)) {
+                  const int at = atomicAdd(&list_n, 1);
+                  list_j[at] = row[u];
+                  list_a[at] = m[u];
+                  list_b[at] = held_x[e][u];
+                  m[u] = held_x[e][u];
+                }
+              if (mine[u] & mask) picked[u] = true;
+            }
+            single = false;
+          }
+        }
+      }
+    }
+    if (single) {
+      const int t = 4095 - (int)(top & 4095);
+      if (tid == 0) pick_key[step] = top;
+      if constexpr (GAP) {
+        uint64_t sb = 0;
+#pragma unroll
+        for (int u = 0; u < ROWS; u++) {
+          const uint64_t k = row[u] == t ? 0ull : key[u];
+          sb = k > sb ? k : sb;
+        }
+        const uint64_t wsb = wave_max_u64(sb);
+        if (lane == 0) red2[w] = wsb;
+      }
+#pragma unroll
+      for (int u = 0; u < ROWS; u++) {
+        const int32_t x = Sr[(size_t)t * n + row[u]];
+        if (live[u] && x > m[u]) {
+          const int at = atomicAdd(&list_n, 1);
+          list_j[at] = row[u];
+          list_a[at] = m[u];
+          list_b[at] = x;
+          m[u] = x;
+        }
+        if (row[u] == t) picked[u] = true;
+      }
+    }
+    lds_barrier();
+    if constexpr (GAP) {
+      if (tid == 0) {
+        uint64_t second = 0;
+        for (int q = 0; q < nthr / 64; q++) second = red2[q] > second ? red2[q] : second;
+        pick_gap[step] = second ? (float)((double)((top >> 12) - (second >> 12)) / kSimScale) : __builtin_inff();
+      }
+    }
+    // ---- (4) the changed columns lower the rows' values ----
+    // (once the largest value fits 32 bits every row's does, and the decreases too: sums modulo 2^32 are
+    // then exact, and the lower ends of the clamps are the same for all rows)
+    const int cnt = __builtin_amdgcn_readfirstlane(list_n);
+    const bool narrow = (top >> 44) == 0;
+    uint64_t dec[ROWS];
+    uint32_t dec32[ROWS], a_sum = 0;
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) { dec[u] = 0; dec32[u] = 0; }
+    auto walk = [&](auto batch_c, int e0) {  // list entries (rows of S) whose loads are in flight together
+      constexpr int NB = decltype(batch_c)::value;
+      int32_t sj[NB][ROWS], a[NB], b[NB];
+#pragma unroll
+      for (int q = 0; q < NB; q++) {
+        const int e = min(e0 + q, cnt - 1);
+        const int32_t *Sj = Sr + (uint32_t)__builtin_amdgcn_readfirstlane(list_j[e]) * n;
+#pragma unroll
+        for (int u = 0; u < ROWS; u++) sj[q][u] = Sj[row[u]];
+        a[q] = __builtin_amdgcn_readfirstlane(list_a[e]);
+        b[q] = e0 + q < cnt ? __builtin_amdgcn_readfirstlane(list_b[e]) : a[q];  // (a repeated entry with a == b adds nothing)
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (narrow) {
+#pragma unroll
+        for (int q = 0; q < NB; q++) {
+          a_sum += (uint32_t)a[q];
+#pragma unroll
+          for (int u = 0; u < ROWS; u++) dec32[u] += (uint32_t)min(max(sj[q][u], a[q]), b[q]);  // a <= b
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < NB; q++)
+#pragma unroll
+          for (int u = 0; u < ROWS; u++) dec[u] += (uint32_t)(min(max(sj[q][u], a[q]), b[q]) - a[q]);
+      }
+    };
+    constexpr int kBatch = 16 / ROWS;
+    int e0 = 0;
+    for (; e0 + kBatch / 2 < cnt; e0 += kBatch) walk(std::integral_constant<int, kBatch>{}, e0);
+    if (e0 < cnt) walk(std::integral_constant<int, kBatch / 2>{}, e0);
+#pragma unroll
+    for (int u = 0; u < ROWS; u++) val[u] -= narrow ? (uint64_t)(uint32_t)(dec32[u] - a_sum) : dec[u];
+    sparse = cnt <= kSparse * taken;
+    want = cnt <= kSparser * taken ? kCandRank : kCandRankDense;
+    step += taken;
+    lds_barrier();  // everyone has read the list and the round's words
+    if (tid == 0) { list_n = 0; cand_n = 0; crowded = 0; threshold = 1; }
+  }
+  lds_barrier();
+  for (int k = tid; k < d_loc; k += nthr) {
+    const size_t at = (size_t)bp * d_loc + k;
+    idx[at] = map.token(p, 4095 - (int)(pick_key[k] & 4095));
+    // the first value is the row sum shifted by the region's size (coverage -1 everywhere)
+    const double value = (double)((pick_key[k] >> 12) - 1) - (k == 0 ? (double)n * kSimScale : 0.0);
+    if (gain_out) gain_out[at] = (float)(value / kSimScale);
+    if constexpr (GAP) gap_out[at] = pick_gap[k];
   }
 }
 
@@ -676,7 +961,7 @@ static int gram_k_split(const Shape &s) {
 
 template <typename T>
 static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, float *gap, char *ws,
-                        const Workspace &w, hipStream_t st, unsigned long long *parts) {
+                        const Workspace &w, hipStream_t st, unsigned long long *parts, bool big_state) {
   int32_t *S = reinterpret_cast<int32_t *>(ws + w.sim);
   RegionMap map{s.W, s.tile_h, s.tile_w, s.W / s.tile_w};
   const int tiles = s.n_loc / 16, units = tiles * (tiles + 1) / 2;
@@ -710,10 +995,32 @@ static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, f
   }
   KernelTimer kt(K_GREEDY, st);
   if (s.n_loc > 256) {  // (regions too large for the register-resident kernel)
-    if (gap)
-      hipLaunchKernelGGL((k_greedy_big<true>), dim3(regions), dim3(kBigThreads), 0, st, S, idx, gain, gap, map, s.P, s.n_loc, s.d_loc);
-    else
-      hipLaunchKernelGGL((k_greedy_big<false>), dim3(regions), dim3(kBigThreads), 0, st, S, idx, gain, gap, map, s.P, s.n_loc, s.d_loc);
+    const int threads = std::min(kBigThreads, (s.n_loc + 63) / 64 * 64);
+    // The first n / kBigFirst picks one launch each (the variant that records gaps: none; without room for the
+    // state - the library's static buffer may be full - the kernel starts from nothing).
+    BigState init{nullptr, nullptr, nullptr};
+    int step0 = 0;
+    if (big_state) {
+      const size_t rows = (size_t)regions * s.n_loc;
+      uint64_t *keys = reinterpret_cast<uint64_t *>(ws + w.big);
+      int32_t *ms = reinterpret_cast<int32_t *>(keys + 3 * rows);
+      const BigState state[2] = {{keys, ms, keys + 2 * rows}, {keys + rows, ms + rows, keys + 2 * rows}};
+      const dim3 grid(regions * (s.n_loc / 16));
+      hipLaunchKernelGGL((k_big_round<true>), grid, dim3(256), 0, st, S, state[1], state[0], s.n_loc, 0);
+      if (!gap) step0 = std::min(s.d_loc, s.n_loc / kBigFirst);
+      for (int k = 0; k < step0; k++)
+        hipLaunchKernelGGL((k_big_round<false>), grid, dim3(256), 0, st, S, state[k & 1], state[(k + 1) & 1], s.n_loc, k);
+      init = state[step0 & 1];
+    }
+#define TOMA_GREEDY_BIG(ROWS, GAP)                                                                            \
+  hipLaunchKernelGGL((k_greedy_big<ROWS, GAP>), dim3(regions), dim3(threads), 0, st, S, idx, gain, gap, map, s.P, \
+                     s.n_loc, s.d_loc, init, step0)
+    if (s.n_loc > kBigThreads) {
+      if (gap) TOMA_GREEDY_BIG(2, true); else TOMA_GREEDY_BIG(2, false);
+    } else {
+      if (gap) TOMA_GREEDY_BIG(1, true); else TOMA_GREEDY_BIG(1, false);
+    }
+#undef TOMA_GREEDY_BIG
     return launch_status();
   }
   switch (s.n_loc / 16) {
@@ -749,11 +1056,15 @@ static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, f
   return launch_status();
 }
 
+size_t big_state_bytes(const Shape &s) {
+  return s.n_loc > 256 ? (size_t)s.B * s.P * s.n_loc * (3 * sizeof(uint64_t) + 2 * sizeof(int32_t)) : 0;
+}
+
 int launch_select(const Shape &s, const void *X, int32_t *idx, float *gain, float *gap, char *ws,
-                  const Workspace &w, hipStream_t st, unsigned long long *parts) {
+                  const Workspace &w, hipStream_t st, unsigned long long *parts, bool big_state) {
   if (s.dtype == TOMA_BF16)
-    return select_typed<bf16_t>(s, static_cast<const bf16_t *>(X), idx, gain, gap, ws, w, st, parts);
-  return select_typed<float>(s, static_cast<const float *>(X), idx, gain, gap, ws, w, st, parts);
+    return select_typed<bf16_t>(s, static_cast<const bf16_t *>(X), idx, gain, gap, ws, w, st, parts, big_state);
+  return select_typed<float>(s, static_cast<const float *>(X), idx, gain, gap, ws, w, st, parts, big_state);
 }
 
 }  // namespace toma

@@ -178,6 +178,31 @@ def test_select_on_random_shapes(oracle):
         done += 1
 
 
+@pytest.mark.parametrize("dtype,tile,d_loc", [
+    ("f32", (17, 16), 272),     # the smallest large region, every token picked (candidates run out)
+    ("bf16", (24, 24), 17),     # stops inside the launches of the first picks
+    ("bf16", (24, 24), 18),     # stops with them
+    ("bf16", (24, 24), 430),    # nine waves
+    ("f32", (32, 32), 1000),    # a full workgroup, nearly every token picked
+    ("f32", (40, 32), 900),     # two rows per thread, the second one partly past the end
+    ("bf16", (64, 32), 700),    # the largest
+])
+def test_select_large_regions_without_gaps(oracle, dtype, tile, d_loc):
+    """Without the leads asked for, large regions take several picks per round: the picks and gains must be
+    those of the kernel that takes them one by one (and records the leads), which the oracle checks above."""
+    th, tw = tile
+    for index, sigma in ((33, 1.5), (34, 3.0)):
+        w = synth.scaled(W["tiny"], name="bigbatch", dtype=dtype, B=2, H=th, W=tw, C=64, tile_h=th, tile_w=tw,
+                         keep=d_loc / (th * tw), heads=1, index=index, sigma=sigma)
+        assert w.d_loc == d_loc
+        print(f"[select large regions, no gaps] {dtype} tile {th}x{tw} d_loc={d_loc} sigma={sigma}", flush=True)
+        dv = tg.Device(w, synth.make_inputs(w), 1)
+        idx, gain = dv.select().copy(), dv.gain.cpu().numpy().copy()
+        dv.gain.zero_()
+        assert np.array_equal(dv.select(gap=False), idx)
+        assert np.array_equal(dv.gain.cpu().numpy(), gain)
+
+
 def test_layer_with_large_regions(oracle):
     """A whole layer call whose selection regions hold 1024 tokens (global merge), against the oracle."""
     w = synth.scaled(W["tiny"], name="biglayer", dtype="bf16", B=2, H=32, W=64, C=128, tile_h=32, tile_w=32, keep=0.25,
@@ -893,6 +918,40 @@ def test_pinv_unmerge_of_rank_deficient_weights(oracle, dtype):
     torch.cuda.synchronize()
     _check_stage("Y (pseudo-inverse unmerge, deficient rank)", tg.host(dv.Y),
                  oracle.unmerge_pinv(d, A, np.maximum(Z, 1e-20), _f64(O), rcond), tol)
+
+
+@pytest.mark.parametrize("dtype,tile,d_loc,C", [
+    ("f32", (4, 4), 1, 32),       # a single destination
+    ("bf16", (8, 6), 5, 96),      # an odd number: one pair of every round plays against the dummy
+    ("f32", (12, 4), 31, 64),     # fewer than sixteen sources in the last tile of neither product, odd
+    ("f32", (16, 8), 96, 32),     # the largest whose eigenvectors fit the LDS
+    ("bf16", (16, 16), 97, 160),  # odd, eigenvectors in global memory, a ragged last block of channels
+    ("f32", (16, 16), 128, 64),   # the largest
+])
+def test_pinv_unmerge_sizes(oracle, dtype, tile, d_loc, C):
+    """The eigen-decomposition and its products at the edges of their tiles, with planted well-conditioned
+    weights (every destination weighs a source of its own most).  fp32: the path computes in double, so the
+    output's rounding (2^-24) is all there is, times the pseudo-inverse's condition (below 100 here)."""
+    th, tw = tile
+    w = synth.scaled(W["tiny"], name="pinv_size", dtype=dtype, B=2, H=th, W=2 * tw, C=C, tile_h=th, tile_w=tw,
+                     keep=d_loc / (th * tw), heads=C // 32, index=31)
+    assert w.d_loc == d_loc
+    print(f"[pinv sizes] {dtype} tile {th}x{tw} Dr={d_loc} C={C}", flush=True)
+    rng = np.random.default_rng(73)
+    d = tg.oracle_desc(oracle, w, w.P)
+    dv = tg.Device(w, synth.make_inputs(w), w.P)
+    A = (rng.uniform(0.0, 0.5, (w.B, w.P, d_loc, w.n_loc)) * (rng.uniform(size=(w.B, w.P, d_loc, w.n_loc)) < 0.1)).astype(np.float32)
+    A[..., np.arange(d_loc), np.arange(d_loc)] += 1.0
+    A = _f64(synth.quantize(w, A))
+    Z = A.sum(axis=3).reshape(w.B, w.D)
+    dv.plant(A, Z)
+    Zf = Z.astype(np.float32).astype(np.float64)
+    O = synth.quantize(w, rng.standard_normal((w.B, w.D, C)).astype(np.float32))
+    dv.O.copy_(tg.dev(O, dtype))
+    tb.toma_unmerge_pinv(dv.desc, dv.A, dv.Z, dv.O, 1e-3, dv.Y, dv.ws)
+    torch.cuda.synchronize()
+    ref = oracle.unmerge_pinv(d, A, Zf, _f64(O), 1e-3)
+    _check_stage("Y", tg.host(dv.Y), ref, 2.0 ** -24 * 100 if dtype == "f32" else 2.0 ** -8)
 
 
 @pytest.mark.parametrize("tile_local", [False, True])
