@@ -137,25 +137,63 @@ __device__ __forceinline__ void pack_probs(Frag<float> &f, const f32x4 &lo, cons
   for (int r = 0; r < 4; r++) { f.v[r] = lo[r]; f.v[4 + r] = hi[r]; }
 }
 
-template <typename T, int DH>
-__global__ __launch_bounds__(256) void k_attn(const T *__restrict__ Q, const T *__restrict__ Kx,
+// Maximum / sum over the four 16-lane rows of a wave without LDS traffic: the gfx950 row-swap
+// instructions exchange odd with even rows (16) and the upper with the lower half (32); after each
+// swap the two results hold the two partners of every lane.
+// Maxima as single instructions: fmaxf() would first copy each operand through v_max(x, x) to
+// quiet signalling NaNs, which scores never are.
+__device__ __forceinline__ float max2_f32(float a, float b) {
+  float d;
+  asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+__device__ __forceinline__ float max3_f32(float a, float b, float c) {
+  float d;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+  return d;
+}
+__device__ __forceinline__ float rows4_max_f32(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float m = max2_f32(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
+  const uint32_t w = __builtin_bit_cast(uint32_t, m);
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return max2_f32(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
+}
+__device__ __forceinline__ float rows4_sum_f32(float v) {
+  const uint32_t u = __builtin_bit_cast(uint32_t, v);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const float m = __builtin_bit_cast(float, (uint32_t)a[0]) + __builtin_bit_cast(float, (uint32_t)a[1]);
+  const uint32_t w = __builtin_bit_cast(uint32_t, m);
+  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
+}
+
+// Register-staged attention, for the head widths whose tiles the load-to-LDS ring cannot take (rows under 128
+// bytes, or a ring beyond the LDS): 64 keys per step, four waves of QT query tiles.  Narrow rows (32-wide heads in
+// bf16) do little work per step, so what bounds them is the step's own chain - loads, barrier, LDS reads,
+// products, softmax: their tiles go through two LDS stages (one barrier per step, a tile's loads have a whole
+// step to land), and where two query tiles per wave would leave fewer than two workgroups per CU each wave takes
+// one.  947 tokens, 33 heads of 32: 28.3 us with one stage and two query tiles, 14.7 us so.
+template <typename T, int DH, int QT>
+__global__ __launch_bounds__(256, DH * sizeof(T) < 128 ? 4 : 1) void k_attn(const T *__restrict__ Q, const T *__restrict__ Kx,
                                              const T *__restrict__ V, T *__restrict__ O, int Lq, int L, int H,
                                              float scale_log2, const float *__restrict__ Zs, int D, T *__restrict__ Oe) {
   constexpr int EPP = 16 / (int)sizeof(T);
   constexpr int LD = DH + EPP;        // LDS row stride (elements) of the K and V tiles [64][DH]
   constexpr int KK = DH / 32;         // fragments along head_dim
   constexpr int DT = DH / 16;         // output tiles along head_dim
-  constexpr int QT = 2;               // query tiles (of 16) per wave
   constexpr int NP = 64 * DH / EPP / 256;
-  __shared__ __align__(16) T Ks[64 * LD];
-  __shared__ __align__(16) T Vs[64 * LD];
+  constexpr int STAGES = DH * (int)sizeof(T) < 128 ? 2 : 1;
+  __shared__ __align__(16) T Ks_[STAGES][64 * LD];
+  __shared__ __align__(16) T Vs_[STAGES][64 * LD];
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   const int h = blockIdx.y, b = blockIdx.z;
   // Lq queries attend to L keys / values (the same tokens in self-attention)
   const size_t head = ((size_t)b * H + h) * L * DH;
   const T *Qh = Q + ((size_t)b * H + h) * Lq * DH, *Kh = Kx + head, *Vh = V + head;
-  const int q_w = blockIdx.x * 128 + w * 32;
+  const int q_w = (blockIdx.x * 4 + w) * (16 * QT);
 
   // queries as B-operand fragments: lane = query column, slots = head_dim 32 kk + 8 g + i
   Frag<T> fq[QT][KK];
@@ -206,13 +244,35 @@ __global__ __launch_bounds__(256) void k_attn(const T *__restrict__ Q, const T *
     }
   };
 
-  fetch(0);
-  for (int key0 = 0; key0 < L; key0 += 64) {
-    __syncthreads();
+  auto put = [&](int st) {
 #pragma unroll
-    for (int i = 0; i < NP; i++) { pkt_store(Ks + lds_off[i], rk[i]); pkt_store(Vs + lds_off[i], rv[i]); }
+    for (int i = 0; i < NP; i++) { pkt_store(Ks_[st] + lds_off[i], rk[i]); pkt_store(Vs_[st] + lds_off[i], rv[i]); }
+  };
+  fetch(0);
+  if constexpr (STAGES == 2) {
+    // (everything asked for so far, the queries too, has landed before the loop's loads begin: a query that might
+    // still be on its way would have every step wait for all loads)
+    wait_vmcnt<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    put(0);
+    if (64 < L) fetch(64);
     __syncthreads();
-    if (key0 + 64 < L) fetch(key0 + 64);
+  }
+  for (int key0 = 0; key0 < L; key0 += 64) {
+    const int st_ = STAGES == 2 ? (key0 >> 6) & 1 : 0;
+    const T *Ks = Ks_[st_], *Vs = Vs_[st_];
+    if constexpr (STAGES == 2) {
+      // every wave is past the barrier that ended the previous step: the other stage is free
+      if (key0 + 64 < L) {
+        put(st_ ^ 1);
+        if (key0 + 128 < L) fetch(key0 + 128);
+      }
+    } else {
+      __syncthreads();
+      put(0);
+      __syncthreads();
+      if (key0 + 64 < L) fetch(key0 + 64);
+    }
 
     // transposed scores: st[kt][qt] holds keys 16 kt + 4 g + r (rows) of query c (column)
     f32x4 st[4][QT];
@@ -230,22 +290,27 @@ __global__ __launch_bounds__(256) void k_attn(const T *__restrict__ Q, const T *
         for (int qt = 0; qt < QT; qt++) mma16(st[kt][qt], fk, fq[qt][kk]);
       }
 
-    const bool tail = key0 + 64 > L;
+    if (key0 + 64 > L) {  // only the last tile can reach past the end (uniform branch)
+#pragma unroll
+      for (int qt = 0; qt < QT; qt++)
+#pragma unroll
+        for (int kt = 0; kt < 4; kt++)
+#pragma unroll
+          for (int r = 0; r < 4; r++)
+            if (key0 + 16 * kt + 4 * g + r >= L) st[kt][qt][r] = -__builtin_inff();
+    }
     Frag<T> fp[QT][2];
 #pragma unroll
     for (int qt = 0; qt < QT; qt++) {
-      float mx = -__builtin_inff();
+      float mx = max3_f32(st[0][qt][0], st[0][qt][1], st[0][qt][2]);
+      mx = max3_f32(mx, st[0][qt][3], st[1][qt][0]);
 #pragma unroll
-      for (int kt = 0; kt < 4; kt++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          float sv = st[kt][qt][r] * scale_log2;
-          if (tail && key0 + 16 * kt + 4 * g + r >= L) sv = -__builtin_inff();
-          st[kt][qt][r] = sv;
-          mx = fmaxf(mx, sv);
-        }
-      mx = fmaxf(mx, wave_xor_f32(mx, 16));
-      mx = fmaxf(mx, wave_xor_f32(mx, 32));
+      for (int kt = 1; kt < 4; kt++) {
+        mx = max3_f32(mx, st[kt][qt][1], st[kt][qt][2]);
+        if (kt < 3) mx = max3_f32(mx, st[kt][qt][3], st[kt + 1][qt][0]);
+        else mx = max2_f32(mx, st[kt][qt][3]);
+      }
+      mx = rows4_max_f32(mx) * scale_log2;
       float m_new = fmaxf(m_run[qt], mx);
       float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_new);
       m_run[qt] = m_new;
@@ -254,7 +319,7 @@ __global__ __launch_bounds__(256) void k_attn(const T *__restrict__ Q, const T *
       for (int kt = 0; kt < 4; kt++)
 #pragma unroll
         for (int r = 0; r < 4; r++) {
-          float pv = __builtin_amdgcn_exp2f(st[kt][qt][r] - m_new);
+          float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][qt][r], scale_log2, -m_new));
           st[kt][qt][r] = pv;
           psum += pv;
         }
@@ -278,6 +343,7 @@ __global__ __launch_bounds__(256) void k_attn(const T *__restrict__ Q, const T *
 #pragma unroll
         for (int qt = 0; qt < QT; qt++) mma16(oacc[dt][qt], fv, fp[qt][u]);
       }
+    if constexpr (STAGES == 2) __syncthreads();
   }
 
   // O[b][q][h * DH + dh]: lane holds query c and head_dim rows 16 dt + 4 g + r
@@ -302,38 +368,6 @@ __global__ __launch_bounds__(256) void k_attn(const T *__restrict__ Q, const T *
       else *reinterpret_cast<u32x4 *>(dst + 16 * dt) = *reinterpret_cast<u32x4 *>(o);
     }
   }
-}
-
-// Maximum / sum over the four 16-lane rows of a wave without LDS traffic: the gfx950 row-swap
-// instructions exchange odd with even rows (16) and the upper with the lower half (32); after each
-// swap the two results hold the two partners of every lane.
-// Maxima as single instructions: fmaxf() would first copy each operand through v_max(x, x) to
-// quiet signalling NaNs, which scores never are.
-__device__ __forceinline__ float max2_f32(float a, float b) {
-  float d;
-  asm("v_max_f32 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
-  return d;
-}
-__device__ __forceinline__ float max3_f32(float a, float b, float c) {
-  float d;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
-  return d;
-}
-__device__ __forceinline__ float rows4_max_f32(float v) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float m = max2_f32(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
-  const uint32_t w = __builtin_bit_cast(uint32_t, m);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return max2_f32(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
-}
-__device__ __forceinline__ float rows4_sum_f32(float v) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float m = __builtin_bit_cast(float, (uint32_t)a[0]) + __builtin_bit_cast(float, (uint32_t)a[1]);
-  const uint32_t w = __builtin_bit_cast(uint32_t, m);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
 }
 
 // The same attention with K and V tiles copied global -> LDS by the load-to-LDS path through a ring
@@ -650,10 +684,16 @@ static void launch_attn(const Shape &s, int Lq, int Lk, const T *Q, const T *K, 
       dim3 grid((Lq + 127) / 128 * s.heads * s.B);
       hipLaunchKernelGGL((k_attn_async<T, DH, 2>), grid, dim3(256), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
     }
-    return;
+  } else {
+    // one query tile per wave where two would leave fewer than two workgroups per CU (narrow rows only)
+    constexpr bool kNarrow = kRowPackets < 8;
+    const bool one = kNarrow && (long long)((Lq + 127) / 128) * s.heads * s.B < 512;
+    const dim3 grid(one ? (Lq + 63) / 64 : (Lq + 127) / 128, s.heads, s.B);
+    if (one)
+      hipLaunchKernelGGL((k_attn<T, DH, kNarrow ? 1 : 2>), grid, dim3(256), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
+    else
+      hipLaunchKernelGGL((k_attn<T, DH, 2>), grid, dim3(256), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
   }
-  dim3 grid((Lq + 127) / 128, s.heads, s.B);
-  hipLaunchKernelGGL((k_attn<T, DH>), grid, dim3(256), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
 }
 
 template <typename T>

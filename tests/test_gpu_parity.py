@@ -675,6 +675,23 @@ def test_attention_shapes_and_output_projection(oracle, dtype, heads, C, L, T):
     _check_stage("O Wo", O2, oracle.attend(_f64(Xm), Xe, *Wts, heads=heads, Wo=_f64(Wo)), tg.TOL[dtype])
 
 
+@pytest.mark.parametrize("heads,L", [(1, 1), (2, 16), (1, 63), (2, 64), (3, 65), (2, 129), (1, 191), (1, 192),
+                                     (128, 240)])
+def test_attention_narrow_heads(oracle, heads, L):
+    """bf16 heads of width 32: one, two and more key tiles with full and ragged ends, and enough heads for the
+    workgroups of two query tiles per wave (2 x 2 x 128 of them)."""
+    C = 32 * heads
+    w = synth.scaled(W["tiny"], name="narrow", dtype="bf16", B=2, H=16, W=16, C=C, tile_h=16, tile_w=16, keep=L / 256,
+                     heads=heads, index=37)
+    assert w.D == L
+    print(f"[narrow heads] {heads} heads, {L} tokens", flush=True)
+    inp = synth.make_inputs(w)
+    dv = tg.Device(w, inp, 1)
+    Xm = synth.quantize(w, np.random.default_rng(38).standard_normal((2, L, C)).astype(np.float32))
+    Wts = [_f64(inp[k]) for k in ("Wq", "Wk", "Wv")]
+    _check_stage("O", dv.attend(Xm=Xm), oracle.attend(_f64(Xm), None, *Wts, heads=heads), tg.TOL["bf16"])
+
+
 @pytest.mark.parametrize("dtype,head_dim,order", [("bf16", 64, "up"), ("bf16", 64, "down"), ("bf16", 128, "up"),
                                                   ("f32", 64, "up")])
 def test_attention_with_drifting_maxima(oracle, dtype, head_dim, order):
