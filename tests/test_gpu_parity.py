@@ -692,35 +692,38 @@ def test_attention_narrow_heads(oracle, heads, L):
     _check_stage("O", dv.attend(Xm=Xm), oracle.attend(_f64(Xm), None, *Wts, heads=heads), tg.TOL["bf16"])
 
 
-@pytest.mark.parametrize("dtype,head_dim,order", [("bf16", 64, "up"), ("bf16", 64, "down"), ("bf16", 128, "up"),
-                                                  ("f32", 64, "up")])
-def test_attention_with_drifting_maxima(oracle, dtype, head_dim, order):
+@pytest.mark.parametrize("dtype,head_dim,order,B,heads", [
+    ("bf16", 64, "up", 1, 1), ("bf16", 64, "down", 1, 1), ("bf16", 128, "up", 1, 1), ("f32", 64, "up", 1, 1),
+    # register-staged tiles: one query tile per wave, two (64 sample-heads x 8 workgroups), wide fp32 rows
+    ("bf16", 32, "up", 1, 1), ("bf16", 32, "down", 1, 1), ("bf16", 32, "up", 8, 8), ("f32", 128, "up", 1, 1),
+    ("f32", 128, "down", 1, 1)])
+def test_attention_with_drifting_maxima(oracle, dtype, head_dim, order, B, heads):
     """Scores whose row maxima keep growing along the keys, slowly for some queries and fast for
     others of the same wave (or are largest at the first keys): the streaming softmax has to move
     its reference point per row and rescale what it has accumulated, over 16 key tiles."""
-    print(f"[attend drift] {dtype} head_dim={head_dim} {order}", flush=True)
+    print(f"[attend drift] {dtype} head_dim={head_dim} {order} {B}x{heads}", flush=True)
     rng = np.random.default_rng(9)
-    C, D, T = head_dim, 256, 768
-    w = synth.scaled(W["tiny"], name="drift", dtype=dtype, B=1, H=16, W=16, C=C, tile_h=16, tile_w=16,
-                     keep=1.0, heads=1, T_extra=T, index=14)
+    C, D, T = heads * head_dim, 256, 768
+    w = synth.scaled(W["tiny"], name="drift", dtype=dtype, B=B, H=16, W=16, C=C, tile_h=16, tile_w=16,
+                     keep=1.0, heads=heads, T_extra=T, index=14)
     assert w.D == D
     inp = synth.make_inputs(w)
     dv = tg.Device(w, inp, 1)
     L = D + T
-    # token j = a_j e_0 + noise with a_j rising from 1 to about 45: with W_q = W_k = I the score of
-    # (i, j) is about a_i a_j, so the maximum of row i grows by about 2.8 a_i per tile of 64 keys
+    # token j = a_j e_0 + noise with a_j rising from 1 to about 45 (in every head): with W_q = W_k = I the score
+    # of (i, j) is about a_i a_j, so the maximum of row i grows by about 2.8 a_i per tile of 64 keys
     a = 1.0 + 0.043 * np.arange(L)
     if order == "down":
         a = a[::-1].copy()
-    U = 0.05 * rng.standard_normal((1, L, C))
-    U[0, :, 0] += a
+    U = 0.05 * rng.standard_normal((B, L, C))
+    U[:, :, ::head_dim] += a[:, None]
     U = synth.quantize(w, U.astype(np.float32))
     eye = np.eye(C, dtype=np.float32)
     Wv = synth.quantize(w, (rng.standard_normal((C, C)) / np.sqrt(C)).astype(np.float32))
     dv.Wq.copy_(tg.dev(eye, dtype)); dv.Wk.copy_(tg.dev(eye, dtype)); dv.Wv.copy_(tg.dev(Wv, dtype))
     dv.Xe.copy_(tg.dev(U[:, D:], dtype))
     O = dv.attend(Xm=U[:, :D])
-    ref = oracle.attend(_f64(U[:, :D]), _f64(U[:, D:]), _f64(eye), _f64(eye), _f64(Wv), heads=1)
+    ref = oracle.attend(_f64(U[:, :D]), _f64(U[:, D:]), _f64(eye), _f64(eye), _f64(Wv), heads=heads)
     _check_stage("O", O, ref, tg.TOL[dtype])
 
 
