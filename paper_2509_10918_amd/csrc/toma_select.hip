@@ -570,8 +570,12 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
 //   (4) the changed columns of all picks go into one list, and every thread lowers its rows' values by
 //       med(S_ij, m_j, m_j') - m_j over the list, reading S_ji = S_ij along row j (coalesced).
 // The first rounds, in which a pick changes most columns, the rounds whose candidates crowd one column
-// and the variant that records gaps take the top candidate alone.  Integer arithmetic throughout: picks
-// and values equal the full rescan of Alg. 2.
+// and the variant that records gaps take the top candidate alone.  Where tokens repeat, that is nearly every
+// round (a token's copies have its value, so candidates overflow, and a pick touches its copies): a search
+// that ends with one pick is not tried again for 1, 3, 7, then 15 rounds.  (8 regions of 1024 tokens in blocks
+// of 4 x 4 alike, 512 picks, whole selection: 1481 us with a search in every round, 820 us so, 1121 us with
+// none; random fields 1065 and 1012 us.)  Integer arithmetic throughout: picks and values equal the full
+// rescan of Alg. 2.
 // 8 regions of 1024 tokens, 512 picks each: 1846 us with one pick per round, 980 us with this and k_big_round.
 // (A batch's loads are requested unguarded, with clamped indices, before the first is used: with a guard around
 // each the compiler waits for every load by itself, which alone costs 450 us.)
@@ -581,6 +585,7 @@ constexpr int kCandRank = 12, kCandRankDense = 6;  // group maxima that reach th
 constexpr int kCandHeld = 8;    // candidates that may exceed one column's coverage
 // changed columns per pick up to which rounds take several picks, and up to which they take them from the longer list
 constexpr int kSparse = 64, kSparser = 12;
+constexpr int kBackMax = 15;    // rounds of one pick between two searches for several that fail, at most
 
 // State of the selection of one large region between kernels: keys (0 = picked), coverage, picks so far.
 struct BigState { uint64_t *key; int32_t *m; uint64_t *pick; };
@@ -723,6 +728,7 @@ __global__ __launch_bounds__(kBigThreads) void k_greedy_big(const int32_t *__res
 
   bool sparse = step0 > 0;  // uniform: the previous round's picks changed few columns each
   int want = kCandRankDense;
+  int back = 0, skip = 0;   // uniform: rounds to leave out after a search for one pick only, how many are left of them
   for (int step = step0; step < d_loc;) {
     // ---- (1) the largest key of every 16 lanes, of all, and the threshold ----
     uint64_t best = 0, key[ROWS];
@@ -744,8 +750,9 @@ __global__ __launch_bounds__(kBigThreads) void k_greedy_big(const int32_t *__res
       lo = max(lo, dpp_u32<kDppRor8>(lo));
       if ((lane & 15) == 0) group_top[tid >> 4] = ((uint64_t)top_hi << 32) | lo;
     }
+    const bool several = sparse && skip == 0;
     if constexpr (!GAP)
-      if (sparse)
+      if (several)
         for (int e = tid; e < kCandMax * kCandMax; e += nthr) dec_pair[e] = 0;
     lds_barrier();
     const uint64_t gk = lane < groups ? group_top[lane] : 0ull;
@@ -757,7 +764,7 @@ __global__ __launch_bounds__(kBigThreads) void k_greedy_big(const int32_t *__res
     int taken = 1;
 
     if constexpr (!GAP) {
-      if (sparse) {
+      if (several) {
         // wave w ranks the maxima of its own four groups (keys are unique unless zero)
 #pragma unroll
         for (int i = 0; i < 4; i++) {
@@ -934,6 +941,8 @@ __global__ __launch_bounds__(kBigThreads) void k_greedy_big(const int32_t *__res
     for (int u = 0; u < ROWS; u++) val[u] -= narrow ? (uint64_t)(uint32_t)(dec32[u] - a_sum) : dec[u];
     sparse = cnt <= kSparse * taken;
     want = cnt <= kSparser * taken ? kCandRank : kCandRankDense;
+    if (several) skip = back = taken > 1 ? 0 : min(2 * back + 1, kBackMax);
+    else skip = max(skip - 1, 0);
     step += taken;
     lds_barrier();  // everyone has read the list and the round's words
     if (tid == 0) { list_n = 0; cand_n = 0; crowded = 0; threshold = 1; }
