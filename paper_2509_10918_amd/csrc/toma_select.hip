@@ -462,6 +462,8 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
       // in the registers where the compiler's own relative addressing keeps it anyway, and only the
       // clamped values are summed per column - the lower ends a are added up once, in a scalar
       // register (32-bit wrap-around is exact here: the true decrease fits the key's 32 bits).
+      // The scalars a and b come from lane reads, two wait states before a vector instruction may read them, and
+      // the compiler puts none in front of inline assembly: the register fetches stand before their first use.
       if (changed) {
         uint32_t q_sum[4] = {0u, 0u, 0u, 0u}, a_sum = 0u;
         do {
@@ -471,13 +473,13 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
           a_sum += (uint32_t)a;
           int32_t q0, q1, q2, q3, bv;
           asm volatile(
-              "v_mov_b32 %[bv], %[b]\n\t"
               "s_set_gpr_idx_on %[c], gpr_idx(SRC0)\n\t"
               "v_mov_b32 %[q0], v0\n\t"
               "v_mov_b32 %[q1], v32\n\t"
               "v_mov_b32 %[q2], v64\n\t"
               "v_mov_b32 %[q3], v96\n\t"
               "s_set_gpr_idx_off\n\t"
+              "v_mov_b32 %[bv], %[b]\n\t"
               "v_med3_i32 %[q0], %[q0], %[a], %[bv]\n\t"
               "v_med3_i32 %[q1], %[q1], %[a], %[bv]\n\t"
               "v_med3_i32 %[q2], %[q2], %[a], %[bv]\n\t"
@@ -506,10 +508,9 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
         const int32_t a = __builtin_amdgcn_readlane(m_old, c), b = __builtin_amdgcn_readlane(m, c);
 #pragma unroll
         for (int v = 0; v < RPL; v++) {
-          // clamp to [a, b] (a < b) as one median instruction; at most one operand may be scalar
-          int32_t cl3;
-          const int32_t bvec = b;
-          asm("v_med3_i32 %0, %1, %2, %3" : "=v"(cl3) : "v"(sv[v][c]), "s"(a), "v"(bvec));
+          // clamp to [a, b] (a < b), in the form that the compiler turns into one median instruction
+          const int32_t x = sv[v][c];
+          const int32_t cl3 = max(min(x, a), min(max(x, a), b));
           dec[v] += (uint32_t)(cl3 - a);
         }
       } while (changed);

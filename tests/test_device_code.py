@@ -16,6 +16,12 @@ from paper_2509_10918_amd import build
 # kind of writer -> kind of reader.  Products differ by their size; 19 is the longest.
 NEEDED = {
     ("product", "vector"): 19,   # matrix product -> vector instruction that reads the result
+    ("product", "lane"): 19,
+    ("scalar", "vector"): 2,     # vector instruction that writes a scalar register -> vector instruction that reads it
+    ("scalar", "memory"): 5,     # -> load or store that takes its address from it
+    ("vector", "lane"): 2,       # vector instruction -> row moves of the result between lanes, reads of single lanes
+    ("slow", "vector"): 1,       # exponential, root, reciprocal -> vector instruction that reads the result
+    ("slow", "lane"): 2,
 }
 HORIZON = 24
 
@@ -38,14 +44,33 @@ class Instr:
         vector = op.startswith("v_")
         memory = op.startswith(("ds_", "global_", "buffer_", "flat_", "scratch_"))
         n_out = 1 if vector or (memory and ("load" in op or "read" in op) and "lds" not in op) else 0
+        if op.startswith(("s_load", "s_mov", "s_add", "s_sub", "s_and", "s_or", "s_lsh", "s_mul", "s_ff1", "s_cselect", "s_min",
+                          "s_max", "s_bfe", "s_lshr", "s_ashr", "s_xor", "s_not", "s_andn2", "s_bcnt")):
+            n_out = 1
+        if op.startswith(("v_add_co", "v_sub_co", "v_addc", "v_subb", "v_div_scale", "v_mad_u64", "v_mad_i64")):
+            n_out = 2
         out, ins = ops[:n_out], ops[n_out:]
         if "swap" in op:
             out = ins = ops
         # (an accumulator may live in the a registers: the other half of the same file)
-        self.writes = set().union(*(_regs(o, k) for o in out for k in "va"), set())
-        self.reads = set().union(*(_regs(o, k) for o in ins for k in "va"), set())
-        self.write_kind = "product" if op.startswith(("v_mfma", "v_smfma")) else None
-        self.read_kind = "vector" if vector else None
+        self.writes = set().union(*(_regs(o, k) for o in out for k in "vas"), set())
+        self.reads = set().union(*(_regs(o, k) for o in ins for k in "vas"), set())
+        if op.startswith("v_") and "vcc" in rest:
+            (self.writes if any("vcc" in o for o in out) else self.reads).add(("s", "vcc"))
+        self.write_kind = self.read_kind = None
+        if vector:
+            self.write_kind = ("product" if op.startswith(("v_mfma", "v_smfma")) else
+                               "slow" if re.match(r"v_(exp|log|rcp|rsq|sqrt|sin|cos)_", op) else "vector")
+            moves = "quad_perm" in rest or "row_" in rest or "permlane" in op or "readlane" in op or "readfirstlane" in op
+            self.read_kind = "lane" if moves else "vector"
+        elif memory:
+            self.read_kind = "memory"
+
+    def kind_of(self, reg):
+        """Kind of this instruction as the writer of `reg` (scalar registers: by a vector instruction only)."""
+        if reg[0] == "s":
+            return "scalar" if self.op.startswith("v_") else None
+        return self.write_kind
 
 
 def _functions(path):
@@ -104,9 +129,8 @@ def short_waits(path):
                         if reg in ins.reads and (ins.inline or was_inline) and age < NEEDED.get((kind, ins.read_kind), 0):
                             found.add((name, ins.line, f"{ins.op} after {age} of {NEEDED[kind, ins.read_kind]} wait states"))
                 state = {k: a + ins.waits for k, a in state.items() if k[0] not in ins.writes and a + ins.waits < HORIZON}
-                if ins.write_kind:
-                    # (the age counts from the writer itself: the next instruction sees 0)
-                    state.update({(r, ins.write_kind, ins.inline): 0 for r in ins.writes})
+                # (the age counts from the writer itself: the next instruction sees 0)
+                state.update({(r, ins.kind_of(r), ins.inline): 0 for r in ins.writes if ins.kind_of(r)})
             for nxt in blocks[n][1]:
                 nxt = labels.get(nxt) if isinstance(nxt, str) else nxt
                 if nxt is None or nxt >= len(blocks):
@@ -139,6 +163,12 @@ def _inline(text):
     (PRODUCT + "v_mov_b32 v4, v1\n" + _inline("v_max_f32 v1, v4, v2"), False),         # another result by then
     # the branch around the masking of the last tile: long on one path, short on the other
     (PRODUCT + "s_cbranch_scc1 .L1\n" + "s_nop 15\ns_nop 15\n.L1:\n" + _inline("v_max_f32 v1, v7, v2"), True),
+    ("v_readlane_b32 s4, v1, s9\ns_mov_b32 s5, 0\n" + _inline("v_mov_b32 v2, s4"), True),
+    ("v_readlane_b32 s4, v1, s9\ns_nop 1\n" + _inline("v_mov_b32 v2, s4"), False),
+    ("v_readlane_b32 s4, v1, s9\ns_mov_b32 s4, 0\n" + _inline("v_mov_b32 v2, s4"), False),   # scalar unit: no wait
+    ("v_readfirstlane_b32 s4, v1\ns_nop 1\n" + _inline("global_load_dwordx4 v[4:7], v2, s[4:5]"), True),
+    (_inline("v_mov_b32 v1, v2") + "s_nop 0\nv_mov_b32_dpp v3, v1 quad_perm:[1,0,3,2]\n", True),
+    ("v_exp_f32 v1, v2\n" + _inline("v_add_f32 v3, v1, v1"), True),
     # round a loop
     (".L1:\n" + _inline("v_max_f32 v1, v7, v2") + PRODUCT + "s_cbranch_scc1 .L1\n", True),
 ])
