@@ -103,7 +103,8 @@ int toma_select(const toma_desc *desc, const void *X, int32_t *idx, float *gain_
  * toma_select for callers that cannot hand over or allocate a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid device allocation): the same selection, same
  * arguments and results, with its scratch (the regions' similarity matrices, B * P * N_loc^2 32-bit
- * words, and for bf16 tokens their fixed-point copy, 4 bytes per element) in a buffer of
+ * words, for bf16 tokens in regions of up to 256 tokens their fixed-point copy, 4 bytes per element,
+ * and for larger regions 32 bytes per token if there is room left for them) in a buffer of
  * TOMA_STATIC_SCRATCH_BYTES that is part of the library's device code and present once on every GPU.
  * No device memory is allocated or freed, at any call.
  *   - Shapes whose scratch exceeds the buffer return TOMA_ERR_WORKSPACE (the SDXL-sized layers fit:

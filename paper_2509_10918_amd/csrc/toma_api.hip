@@ -66,7 +66,6 @@ void plan_workspace(const Shape &s, Workspace *w) {
   if (weights_single_pass(s.Nr, s.Dr, s.C, s.B * s.R, (int)es)) w->z_parts = s.Nr / 32;  // one partial row sum per 32-source workgroup
   w->sim = take((size_t)s.B * s.P * s.n_loc * s.n_loc * sizeof(float));
   w->gram = take(gram_i8_workspace_bytes(s));  // limb planes, norms and flags of the int8 similarity kernel
-  w->big = take(big_state_bytes(s));
   w->stats = take((size_t)s.B * s.N * w->stat_parts * 2 * sizeof(float));
   w->lse = take((size_t)s.B * s.N * sizeof(float));
   w->zpart = take((size_t)s.B * s.D * w->z_parts * sizeof(float));
@@ -102,6 +101,8 @@ void plan_workspace(const Shape &s, Workspace *w) {
   w->z_in_merge = gemm_async_fits(s.Dr, s.C, s.Nr, (int)es) &&
                   plan_map_product(s.Dr, s.C, s.Nr, s.B * s.R, (int)es, false, true, w->occ_sb != 0).nsplit == 1;
   w->total = off;
+  w->big = w->stats;  // (the first section that the selection does not use)
+  w->big_state = w->big + big_state_bytes(s) <= w->total;  // (always: stats and its like in fcache take 32 bytes per token)
 }
 
 static bool misaligned(const void *p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }
@@ -225,9 +226,8 @@ TOMA_API int toma_select_static(const toma_desc *desc, const void *X, int32_t *i
   char *buf = nullptr;
   rc = static_scratch(&buf);
   if (rc != TOMA_OK) return rc;
-  // (a large region's state only where the scratch has room left for it: the kernels do without)
-  const bool big_state = w.big + up256(big_state_bytes(s)) <= (size_t)TOMA_STATIC_SCRATCH_BYTES;
-  return launch_select(s, X, idx, gain_opt, gap_opt, buf, w, static_cast<hipStream_t>(stream), nullptr, big_state);
+  w.big_state = w.big + big_state_bytes(s) <= (size_t)TOMA_STATIC_SCRATCH_BYTES;
+  return launch_select(s, X, idx, gain_opt, gap_opt, buf, w, static_cast<hipStream_t>(stream));
 }
 
 TOMA_API int toma_merge(const toma_desc *desc, const void *X, const int32_t *idx, void *A, float *Z, void *amap,

@@ -21,7 +21,11 @@ struct Shape {
 
 // Offsets (bytes) of the scratch sections inside the caller's workspace.
 struct Workspace {
-  size_t sim, gram, big, stats, lse, zpart, os, q, k, v, oh, xm, o, split, pinv, fcache, total;
+  size_t sim, gram, stats, lse, zpart, os, q, k, v, oh, xm, o, split, pinv, fcache, total;
+  // state of large regions between the selection's kernels: in the room of the sections behind it, which only
+  // later stages use.  big_state: the scratch at hand has room for it (the kernels do without where it has not)
+  size_t big;
+  bool big_state;
   int stat_parts, z_parts;
   // occupancy map of A, kept by the caller next to (A, Z): blocks of kOccDest destinations x kOccSrc
   // sources per merge region (0: this shape uses none)
@@ -137,9 +141,8 @@ int launch_gram_i8(const Shape &s, const void *X, int32_t *S, char *ws_part, con
                    const uint8_t **flag_out, hipStream_t st);
 // gain, gap: optional outputs (null: not wanted); parts: null, or where the profiling variant of the
 // greedy kernel leaves the clocks of the parts of its rounds (eight words per region and wave)
-// big_state: w.big holds the state of large regions between kernels (false: no room for it)
 int launch_select(const Shape &s, const void *X, int32_t *idx, float *gain, float *gap, char *ws,
-                  const Workspace &w, hipStream_t st, unsigned long long *parts = nullptr, bool big_state = true);
+                  const Workspace &w, hipStream_t st, unsigned long long *parts = nullptr);
 // keys, coverage and picks of regions of more than 256 tokens between the selection's kernels
 size_t big_state_bytes(const Shape &s);
 // Pass 1 of the merge weights alone: stats[region][source][part] = (largest logit, sum of exponentials)

@@ -971,7 +971,7 @@ static int gram_k_split(const Shape &s) {
 
 template <typename T>
 static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, float *gap, char *ws,
-                        const Workspace &w, hipStream_t st, unsigned long long *parts, bool big_state) {
+                        const Workspace &w, hipStream_t st, unsigned long long *parts) {
   int32_t *S = reinterpret_cast<int32_t *>(ws + w.sim);
   RegionMap map{s.W, s.tile_h, s.tile_w, s.W / s.tile_w};
   const int tiles = s.n_loc / 16, units = tiles * (tiles + 1) / 2;
@@ -1010,7 +1010,7 @@ static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, f
     // state - the library's static buffer may be full - the kernel starts from nothing).
     BigState init{nullptr, nullptr, nullptr};
     int step0 = 0;
-    if (big_state) {
+    if (w.big_state) {
       const size_t rows = (size_t)regions * s.n_loc;
       uint64_t *keys = reinterpret_cast<uint64_t *>(ws + w.big);
       int32_t *ms = reinterpret_cast<int32_t *>(keys + 3 * rows);
@@ -1071,10 +1071,10 @@ size_t big_state_bytes(const Shape &s) {
 }
 
 int launch_select(const Shape &s, const void *X, int32_t *idx, float *gain, float *gap, char *ws,
-                  const Workspace &w, hipStream_t st, unsigned long long *parts, bool big_state) {
+                  const Workspace &w, hipStream_t st, unsigned long long *parts) {
   if (s.dtype == TOMA_BF16)
-    return select_typed<bf16_t>(s, static_cast<const bf16_t *>(X), idx, gain, gap, ws, w, st, parts, big_state);
-  return select_typed<float>(s, static_cast<const float *>(X), idx, gain, gap, ws, w, st, parts, big_state);
+    return select_typed<bf16_t>(s, static_cast<const bf16_t *>(X), idx, gain, gap, ws, w, st, parts);
+  return select_typed<float>(s, static_cast<const float *>(X), idx, gain, gap, ws, w, st, parts);
 }
 
 }  // namespace toma

@@ -52,6 +52,27 @@ def test_workspace_bytes_and_shape_errors():
     assert tb.toma_workspace_bytes(None, None) == 0
 
 
+@pytest.mark.parametrize("B,H,W,C,th,tw,d_loc,R,dtype,select_bytes,layer_bytes", [
+    (2, 64, 64, 640, 32, 32, 512, 1, "bf16", 79822848, 107022848),
+    (2, 64, 64, 640, 32, 32, 512, 4, "bf16", 45744128, 72944128),
+    (1, 32, 32, 64, 32, 32, 16, 1, "bf16", 4255744, 4315904),
+    (2, 64, 64, 64, 64, 32, 1, 1, "bf16", 67505408, 67606528),
+    (3, 48, 48, 96, 24, 24, 100, 1, "f32", 21616128, 24364288),
+    (1, 17, 16, 32, 17, 16, 272, 1, "bf16", 390144, 502784),
+])
+def test_large_regions_need_no_more_workspace(B, H, W, C, th, tw, d_loc, R, dtype, select_bytes, layer_bytes):
+    """Sizes that were enough for regions of more than 256 tokens stay enough: what their selection keeps between
+    its kernels lies in room of the stages behind it."""
+    L = tb.lib()
+    d = tb.make_desc(B, H, W, C, th, tw, d_loc, R, 0.1, dtype)
+    a = tb.toma_attn_desc(C // 32, 32, 77)
+    assert tb.toma_workspace_bytes(d, None) <= select_bytes
+    assert tb.toma_workspace_bytes(d, a) <= layer_bytes
+    ws, x = 256 * 1024, 1 << 20   # fake addresses: the missing X is found after the workspace was taken
+    assert L.toma_select(ctypes.addressof(d), None, x, None, None, ws, select_bytes, None) == 1
+    assert L.toma_select(ctypes.addressof(d), None, x, None, None, ws, 4096, None) == 4
+
+
 def test_argument_errors_are_reported_before_any_launch():
     L = tb.lib()
     d = _d()
