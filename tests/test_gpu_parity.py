@@ -67,7 +67,7 @@ def test_select_matches_oracle_exactly(oracle, cases, name):
 
 @pytest.mark.parametrize("n_loc_shape,d_loc", [((4, 4), 16), ((4, 4), 1), ((8, 6), 7), ((16, 16), 256),
                                                ((10, 16), 33), ((16, 13), 100)])
-def test_select_region_sizes(oracle, n_loc_shape, d_loc):
+def test_select_region_and_destination_counts(oracle, n_loc_shape, d_loc):
     th, tw = n_loc_shape
     w = synth.scaled(W["tiny"], name="sel", B=2, H=2 * th, W=3 * tw, C=32, tile_h=th, tile_w=tw,
                      keep=d_loc / (th * tw), index=11)
@@ -555,6 +555,33 @@ def test_merge_unmerge_of_planted_weights(oracle, dtype, case):
     _check_stage("Y (layer, cached A)", Yl, ref["Y"], tol)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tile,d_loc", [((4, 4), 1), ((8, 6), 33), ((8, 10), 65), ((14, 8), 97), ((16, 9), 129),
+                                        ((16, 13), 161), ((16, 15), 193)])
+def test_merge_unmerge_of_few_k_steps(oracle, dtype, tile, d_loc):
+    """Merge (K = sources of a region) and unmerge (K = destinations) whose K is no multiple of the K step (64
+    elements in bf16, 32 in fp32): one to four steps and more, each with a ragged end, against dense weights.
+    fp32: at most 256 roundings of 2^-24 per sum; bf16 (8 significant bits): the rounding of the result, and for
+    the unmerge of O / Z before it, 2^-8 each."""
+    th, tw = tile
+    w = synth.scaled(W["tiny"], name="ksteps", dtype=dtype, B=2, H=th, W=2 * tw, C=96, tile_h=th, tile_w=tw,
+                     keep=d_loc / (th * tw), heads=3, index=43)
+    assert w.d_loc == d_loc
+    print(f"[k steps] {dtype} tile {th}x{tw} d_loc={d_loc}", flush=True)
+    inp = synth.make_inputs(w)
+    rng = np.random.default_rng(44)
+    d = tg.oracle_desc(oracle, w, w.P)
+    dv = tg.Device(w, inp, w.P)
+    A = _f64(synth.quantize(w, rng.uniform(0.0, 1.0, (w.B, w.P, d_loc, w.n_loc)).astype(np.float32)))
+    Z = A.sum(axis=3).reshape(w.B, w.D)
+    dv.plant(A, Z)
+    tol = 256 * 2.0 ** -24 if dtype == "f32" else 2.0 ** -8
+    _check_stage("Xm", dv.merge_cached(), oracle.merge(d, _f64(inp["X"]), A, Z), tol)
+    tol = tol if dtype == "f32" else 2 * tol
+    O = synth.quantize(w, rng.standard_normal((w.B, w.D, w.C)).astype(np.float32))
+    _check_stage("Y", dv.unmerge(O=O), oracle.unmerge(d, A, Z, _f64(O)), tol)
+
+
 @pytest.mark.parametrize("tile_local", [False, True])
 @pytest.mark.parametrize("name", list(CASES))
 def test_layer_chained_and_reuse(oracle, cases, name, tile_local):
@@ -788,7 +815,10 @@ def test_attention_with_drifting_maxima(oracle, dtype, head_dim, order, B, heads
 
 
 @pytest.mark.parametrize("dtype,rows,C,hidden", [("f32", 200, 64, 256), ("bf16", 1000, 128, 512),
-                                                  ("bf16", 333, 96, 160), ("bf16", 2 * 2048, 640, 2560)])
+                                                  ("bf16", 333, 96, 160), ("bf16", 2 * 2048, 640, 2560),
+                                                  # one to four K steps of 64, the last one half full
+                                                  ("bf16", 65, 32, 96), ("bf16", 63, 96, 32), ("bf16", 200, 160, 224),
+                                                  ("bf16", 1, 224, 160)])
 def test_mlp_module(oracle, dtype, rows, C, hidden):
     """gelu(X W1) W2 against the oracle: ragged row counts, a width the load-to-LDS GEMM cannot take
     (96 channels in bf16) and the SDXL stage-1 size."""
@@ -965,13 +995,20 @@ def test_pinv_unmerge(oracle, cases, case, tile_local):
     assert tg.max_rel(oracle.unmerge(d, A, np.maximum(Z, 1e-20), _f64(O)), Y_ref) > 10 * tol
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_pinv_unmerge_of_rank_deficient_weights(oracle, dtype):
+@pytest.mark.parametrize("dtype,tile,d_loc", [
+    ("bf16", (8, 8), 32), ("f32", (8, 8), 32),
+    ("f32", (8, 8), 31),        # odd: a pair with the dummy in every round
+    ("bf16", (16, 16), 97),     # eigenvectors in global memory, odd
+    ("f32", (16, 16), 128),
+])
+def test_pinv_unmerge_of_rank_deficient_weights(oracle, dtype, tile, d_loc):
     """Planted merge matrices whose rows are dependent in every way the cut has to handle: a destination
     with no weight (zero row), two destinations with identical rows, and a row that is a combination of
     two others - against numpy's pseudo-inverse (least-squares, minimum-norm answer)."""
-    w = synth.scaled(W["tiny"], name="pinv_planted", dtype=dtype, B=2, H=16, W=16, C=64, tile_h=8, tile_w=8, keep=0.5,
-                     heads=1, index=27)
+    th, tw = tile
+    w = synth.scaled(W["tiny"], name="pinv_planted", dtype=dtype, B=2, H=2 * th, W=2 * tw, C=64, tile_h=th, tile_w=tw,
+                     keep=d_loc / (th * tw), heads=1, index=27)
+    assert w.d_loc == d_loc
     inp = synth.make_inputs(w)
     R, tol = w.P, tg.TOL[dtype]
     rng = np.random.default_rng(72)
@@ -1032,6 +1069,41 @@ def test_pinv_unmerge_sizes(oracle, dtype, tile, d_loc, C):
     torch.cuda.synchronize()
     ref = oracle.unmerge_pinv(d, A, Zf, _f64(O), 1e-3)
     _check_stage("Y", tg.host(dv.Y), ref, 2.0 ** -24 * 100 if dtype == "f32" else 2.0 ** -8)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("dtype,d_loc", [("bf16", 21), ("f32", 32)])
+def test_pinv_unmerge_of_values_that_are_not_finite(oracle, dtype, d_loc, bad):
+    """An infinity or NaN in one channel of O spoils that channel of its own region and nothing else; there, a
+    source without any weight still gets zero."""
+    w = synth.scaled(W["tiny"], name="pinv_inf", dtype=dtype, B=2, H=8, W=16, C=96, tile_h=8, tile_w=8, keep=d_loc / 64,
+                     heads=3, index=45)
+    assert w.d_loc == d_loc
+    print(f"[pinv non-finite] {dtype} d_loc={d_loc} {bad}", flush=True)
+    rng = np.random.default_rng(46)
+    d = tg.oracle_desc(oracle, w, w.P)
+    dv = tg.Device(w, synth.make_inputs(w), w.P)
+    A = (rng.uniform(0.0, 0.5, (w.B, w.P, d_loc, 64)) * (rng.uniform(size=(w.B, w.P, d_loc, 64)) < 0.1)).astype(np.float32)
+    A[..., np.arange(d_loc), np.arange(d_loc)] += 1.0
+    A[1, 0, :, 60] = 0.0                                    # a source with no weight, in the spoiled region
+    A = _f64(synth.quantize(w, A))
+    Z = A.sum(axis=3).reshape(w.B, w.D)
+    dv.plant(A, Z)
+    O = synth.quantize(w, rng.standard_normal((w.B, w.D, w.C)).astype(np.float32))
+    ref = oracle.unmerge_pinv(d, A, Z.astype(np.float32).astype(np.float64), _f64(O), 1e-3)
+    O[1, 5, 40] = bad                                       # sample 1, region 0 (its rows are 0 .. d_loc - 1)
+    dv.O.copy_(tg.dev(O, dtype))
+    tb.toma_unmerge_pinv(dv.desc, dv.A, dv.Z, dv.O, 1e-3, dv.Y, dv.ws)
+    torch.cuda.synchronize()
+    Y = tg.host(dv.Y)
+    tokens = tg.source_tokens(dv.desc)[0]                   # grid index of region 0's sources
+    spoiled = np.zeros(Y.shape, dtype=bool)
+    spoiled[1, tokens, 40] = True
+    weight = A[1, 0].sum(axis=0) > 0
+    assert not weight[60] and not np.any(np.isfinite(Y[1, tokens[weight], 40]))
+    assert np.all(Y[1, tokens[~weight], 40] == 0.0)
+    Y[spoiled] = ref[spoiled] = 0.0
+    _check_stage("Y elsewhere", Y, ref, 2.0 ** -24 * 100 if dtype == "f32" else 2.0 ** -8)
 
 
 @pytest.mark.parametrize("tile_local", [False, True])

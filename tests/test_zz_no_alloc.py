@@ -49,6 +49,28 @@ def test_select_static_matches_select_twice_then_smaller(oracle):
         assert not bad
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,Wd,tile,d_loc", [
+    (2, 64, 64, (32, 32), 40),    # eight regions of 1024: the similarities fill the buffer, no room for the regions' state
+    (1, 64, 32, (32, 32), 512),   # room for it
+    (2, 48, 24, (24, 24), 100),
+])
+def test_select_static_of_large_regions(B, H, Wd, tile, d_loc):
+    th, tw = tile
+    w = synth.scaled(W["sdxl1"], name="static_large", B=B, H=H, W=Wd, C=64, tile_h=th, tile_w=tw, keep=d_loc / (th * tw),
+                     heads=1, index=47)
+    assert w.d_loc == d_loc
+    print(f"[static] {B}x{w.P} regions of {w.n_loc}, d_loc={d_loc}", flush=True)
+    ref_idx = _both(w)
+    # and the kernel that takes several picks per round (no leads asked for)
+    dv = tg.Device(w, synth.make_inputs(w), 1)
+    rc = tb.lib().toma_select_static(ctypes.addressof(dv.desc), dv.X.data_ptr(), dv.idx.data_ptr(), None, None,
+                                     torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, tb.status_string(rc)
+    torch.cuda.synchronize()
+    assert np.array_equal(dv.idx.cpu().numpy(), ref_idx)
+
+
 def test_select_static_refuses_what_does_not_fit():
     """Host-side checks only: nothing is launched."""
     L = tb.lib()
