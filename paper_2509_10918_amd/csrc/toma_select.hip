@@ -456,43 +456,34 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
     const unsigned long long t3 = now();
     if constexpr (CLOCKS) clk[6] += (unsigned)__builtin_popcount(changed);
     if constexpr (!WIDE && RPL == 4) {
-      // The common case (a region of 208 to 256 tokens, keys in 32-bit words) written out as
-      // instructions: the column's four registers are fetched under one switch of the register-index
-      // mode (instead of one switch on and off around every fetch), each bank asked for
-      // in the registers where the compiler's own relative addressing keeps it anyway, and only the
-      // clamped values are summed per column - the lower ends a are added up once, in a scalar
-      // register (32-bit wrap-around is exact here: the true decrease fits the key's 32 bits).
-      // The scalars a and b come from lane reads, two wait states before a vector instruction may read them, and
-      // the compiler puts none in front of inline assembly: the register fetches stand before their first use.
+      // The common case (a region of 208 to 256 tokens, keys in 32-bit words): the column's four registers are
+      // fetched under one switch of the register-index mode (instead of one switch on and off around every
+      // fetch), each bank asked for in the registers where the compiler's own relative addressing keeps it
+      // anyway, and only the clamped values are summed per column - the lower ends a are added up once, in a
+      // scalar register (32-bit wrap-around is exact here: the true decrease fits the key's 32 bits).
+      // The fetches stand before the lane reads: the switch of the index mode waits for lane reads ahead of it.
+      // What uses the scalars is left to the compiler, which knows that two wait states belong between.
       if (changed) {
         uint32_t q_sum[4] = {0u, 0u, 0u, 0u}, a_sum = 0u;
         do {
           const int c = __builtin_ctz(changed);
-          changed &= changed - 1;
-          const int32_t a = __builtin_amdgcn_readlane(m_old, c), b = __builtin_amdgcn_readlane(m, c);
-          a_sum += (uint32_t)a;
-          int32_t q0, q1, q2, q3, bv;
+          int32_t q[4];
           asm volatile(
               "s_set_gpr_idx_on %[c], gpr_idx(SRC0)\n\t"
               "v_mov_b32 %[q0], v0\n\t"
               "v_mov_b32 %[q1], v32\n\t"
               "v_mov_b32 %[q2], v64\n\t"
               "v_mov_b32 %[q3], v96\n\t"
-              "s_set_gpr_idx_off\n\t"
-              "v_mov_b32 %[bv], %[b]\n\t"
-              "v_med3_i32 %[q0], %[q0], %[a], %[bv]\n\t"
-              "v_med3_i32 %[q1], %[q1], %[a], %[bv]\n\t"
-              "v_med3_i32 %[q2], %[q2], %[a], %[bv]\n\t"
-              "v_med3_i32 %[q3], %[q3], %[a], %[bv]\n\t"
-              "v_add_u32 %[d0], %[d0], %[q0]\n\t"
-              "v_add_u32 %[d1], %[d1], %[q1]\n\t"
-              "v_add_u32 %[d2], %[d2], %[q2]\n\t"
-              "v_add_u32 %[d3], %[d3], %[q3]"
-              : [d0] "+v"(q_sum[0]), [d1] "+v"(q_sum[1]), [d2] "+v"(q_sum[2]), [d3] "+v"(q_sum[3]), [q0] "=&v"(q0),
-                [q1] "=&v"(q1), [q2] "=&v"(q2), [q3] "=&v"(q3), [bv] "=&v"(bv)
-              : [c] "s"(c), [a] "s"(a), [b] "s"(b), "{v[0:31]}"(sv[0]), "{v[32:63]}"(sv[1]), "{v[64:95]}"(sv[2]),
-                "{v[96:127]}"(sv[RPL == 4 ? 3 : 0])
+              "s_set_gpr_idx_off"
+              : [q0] "=&v"(q[0]), [q1] "=&v"(q[1]), [q2] "=&v"(q[2]), [q3] "=&v"(q[3])
+              : [c] "s"(c), "{v[0:31]}"(sv[0]), "{v[32:63]}"(sv[1]), "{v[64:95]}"(sv[2]), "{v[96:127]}"(sv[RPL == 4 ? 3 : 0])
               : "m0");
+          __builtin_amdgcn_sched_barrier(0);
+          const int32_t a = __builtin_amdgcn_readlane(m_old, c), b = __builtin_amdgcn_readlane(m, c);
+          changed &= changed - 1;
+          a_sum += (uint32_t)a;
+#pragma unroll
+          for (int v = 0; v < 4; v++) q_sum[v] += (uint32_t)max(min(q[v], a), min(max(q[v], a), b));  // a median instruction
         } while (changed);
 #pragma unroll
         for (int v = 0; v < 4; v++)
@@ -504,13 +495,17 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
       for (int v = 0; v < RPL; v++) dec[v] = 0;
       do {
         const int c = __builtin_ctz(changed);
-        changed &= changed - 1;
+        // (the register fetches first: the switch of the index mode waits for lane reads before it)
+        int32_t x[RPL];
+#pragma unroll
+        for (int v = 0; v < RPL; v++) x[v] = sv[v][c];
+        __builtin_amdgcn_sched_barrier(0);
         const int32_t a = __builtin_amdgcn_readlane(m_old, c), b = __builtin_amdgcn_readlane(m, c);
+        changed &= changed - 1;
 #pragma unroll
         for (int v = 0; v < RPL; v++) {
           // clamp to [a, b] (a < b), in the form that the compiler turns into one median instruction
-          const int32_t x = sv[v][c];
-          const int32_t cl3 = max(min(x, a), min(max(x, a), b));
+          const int32_t cl3 = max(min(x[v], a), min(max(x[v], a), b));
           dec[v] += (uint32_t)(cl3 - a);
         }
       } while (changed);
