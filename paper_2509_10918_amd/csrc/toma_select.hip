@@ -1,7 +1,7 @@
 // Destination selection: cosine similarity inside each region and the greedy facility-location
 // pick sequence (paper Sec. 4.1, Eq. 2, Alg. 2; regions as in Alg. 3 step 1).
 //
-// Two kernels:
+// Kernels (bf16 tokens in regions of up to 256 take their similarities from the int8 matrix cores, toma_gram_i8.hip):
 //   k_gram    S = cos(x_i, x_j) per region with the fp64 matrix cores (v_mfma_f64_16x16x4_f64):
 //             products of stored bf16 / fp32 values are exact in double, so S is the similarity
 //             to ~1e-16 before it is rounded once to the nearest multiple of 2^-30 and stored as
@@ -12,6 +12,8 @@
 //   k_greedy  one workgroup per (sample, region); the region's whole S (up to 256 x 256 words)
 //             lives in the workgroup's vector registers and the rows' values are kept up to date
 //             incrementally (see the comment at the kernel).
+//   k_big_round, k_greedy_big  the same for regions of more than 256 tokens, S in memory: the first
+//             picks as launches over the whole chip, the others in one workgroup per region.
 #include <algorithm>
 #include <type_traits>
 
@@ -572,7 +574,11 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
 // of 4 x 4 alike, 512 picks, whole selection: 1481 us with a search in every round, 820 us so, 1121 us with
 // none; random fields 1065 and 1012 us.)  Integer arithmetic throughout: picks and values equal the full
 // rescan of Alg. 2.
-// 8 regions of 1024 tokens, 512 picks each: 1846 us with one pick per round, 980 us with this and k_big_round.
+// 8 regions of 1024 tokens, 512 picks each: 1846 us with one pick per round; 832 us with this, in 74 rounds, and
+// 106 us in k_big_round's launches before.  64 of the rounds search, 14 candidates each, in about 17000 clocks; 42
+// changed columns per round take 8700 clocks.  The row reads of both come to under 20 GB/s per region: the chain of
+// barriers and dependent loads is what counts.  Whole selections, similarities included, with one pick per round
+// and so: 8 regions of 576 tokens 869 and 546 us, 4 regions of 2048 tokens 5241 and 2328 us.
 // (A batch's loads are requested unguarded, with clamped indices, before the first is used: with a guard around
 // each the compiler waits for every load by itself, which alone costs 450 us.)
 constexpr int kBigRegion = 2048, kBigThreads = 1024;
@@ -592,6 +598,9 @@ struct BigState { uint64_t *key; int32_t *m; uint64_t *pick; };
 // FIRST: no pick, the rows' values under the starting coverage.  The state is double-buffered (in -> out).
 // 8 regions of 1024 tokens: 10 us per launch, where the single workgroup took 200 us for the first values and
 // 33 us per pick for the next seven; from about the eighth pick on it is the faster one (7 us, 4 us after the 32nd).
+// n / 128 picks this way is the best of n / 32, n / 64, n / 128, n / 256 and none at three sizes (whole selections,
+// us): 8 regions of 576 tokens 600, 592, 585, 600, 655; of 1024 tokens 1142, 1095, 1087, 1093, 1258; 4 regions of 2048
+// tokens 2798, 2616, 2591, 2637, 3331.
 constexpr int kBigFirst = 128;
 template <bool FIRST>
 __global__ __launch_bounds__(256) void k_big_round(const int32_t *__restrict__ S, BigState in, BigState out, int n, int step) {
