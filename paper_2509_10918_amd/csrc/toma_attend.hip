@@ -3,18 +3,21 @@
 //
 //   k_gemm<QkvPol>   Q, K, V = U W  (one launch, blockIdx.z picks the weight), written head-major
 //                    [B][heads][L][head_dim] so that every head is a dense matrix.
-//   k_attn_async     flash-style attention: 16 queries per wave, four to twelve waves per workgroup
-//                    (chosen per launch), 64 keys per step through a ring of K / V tiles in LDS,
-//                    online softmax, nothing of size L x L ever stored.  (k_attn: the same with
-//                    register-staged tiles, for head widths whose ring does not fit.)
+//   k_attn_pipe, k_attn_pipe16   (toma_attn_pipe.h) flash-style attention of 64- and 128-wide bf16 heads: 64 keys per
+//                    step through a ring of K / V tiles in LDS, online softmax, nothing of size L x L ever stored;
+//                    32 or 16 queries per wave and four to twelve waves per workgroup, chosen per launch.
+//   k_attn_async     the same for fp32 heads of up to 64 channels: 16 queries per wave.  (k_attn: with register-staged
+//                    tiles, for head widths whose ring does not fit or whose rows are under 128 bytes.)
 //                    The score tile is computed TRANSPOSED (keys x queries): its accumulator
 //                    layout (lane = query, registers = 4 consecutive keys) is then already the
 //                    B-operand layout of the second product O^T += V^T P^T, so probabilities go
 //                    from accumulators straight back into the matrix cores without touching LDS.
 //                    V^T fragments come from the row-major V tile through the LDS transpose read.
 //   k_gemm<ProjPol>  optional output projection.
+// bf16 queries leave the projection multiplied by log2(e) / sqrt(head width): a score is then an exponent of two.
 #include <type_traits>
 
+#include "toma_attn_pipe.h"
 #include "toma_gemm.h"
 #include "toma_internal.h"
 
@@ -29,6 +32,7 @@ template <typename T> struct QkvPol {
   T *out[3];
   int B, D, Tx, L, C, H, dh, dh_sh;  // dh_sh = log2(dh), or -1 if dh is not a power of two
   int Kin;                           // width of the input rows (C for self-attention; the context's for cross-attention keys / values)
+  float scale0;                      // factor of the first output (bf16 queries leave in the units of the attention's exponent)
   __device__ __forceinline__ GemmCtx setup(int bz) const { return GemmCtx{B * L, C, Kin, 0, 0, bz}; }
   __device__ __forceinline__ bool a_linear(int) const { return true; }
   __device__ __forceinline__ bool b_linear(int) const { return true; }
@@ -46,6 +50,7 @@ template <typename T> struct QkvPol {
     // (divisions are dear here: the head width is a power of two, and the sample of a row follows
     // from the sample of the wave tile's first row, which is the same for all lanes)
     T *o = out[x.z];
+    const float sc = x.z == 0 ? scale0 : 1.0f;
     const int L_ = L, H_ = H, dh_ = dh, sh = dh_sh;
     const int b0 = m_w / L_, l0 = m_w - b0 * L_;
     store_rows<T, TM, TN>(acc, m_w, n_w, lane, x.M, x.N,
@@ -56,7 +61,7 @@ template <typename T> struct QkvPol {
                     return o + ((size_t)b * H_ * L_ + l) * dh_;
                   },
                   [=](int n) { const int h = sh >= 0 ? n >> sh : n / dh_; return (size_t)h * L_ * dh_ + (n - h * dh_); },
-                  [](int) { return 1.0f; });
+                  [=](int) { return sc; });
   }
 };
 
@@ -135,33 +140,6 @@ __device__ __forceinline__ void pack_probs(Frag<bf16_t> &f, const f32x4 &lo, con
 __device__ __forceinline__ void pack_probs(Frag<float> &f, const f32x4 &lo, const f32x4 &hi) {
 #pragma unroll
   for (int r = 0; r < 4; r++) { f.v[r] = lo[r]; f.v[4 + r] = hi[r]; }
-}
-
-// Maximum / sum over the four 16-lane rows of a wave without LDS traffic: the gfx950 row-swap
-// instructions exchange odd with even rows (16) and the upper with the lower half (32); after each
-// swap the two results hold the two partners of every lane.
-// Maxima as single instructions: fmaxf() would first copy each operand through v_max(x, x) to quiet signalling
-// NaNs; the NaN-propagating maximum (v_maximum3_f32) takes operands as they are, and a score that is NaN makes
-// its query's row NaN either way.  Builtins and no inline assembly: the compiler puts no wait states between a
-// matrix product and inline assembly that reads its result (8 are due after a 16 x 16 x 32 bf16 product).
-// The same speed as v_max3_f32 written as assembly.
-__device__ __forceinline__ float max2_f32(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-__device__ __forceinline__ float max3_f32(float a, float b, float c) { return max2_f32(max2_f32(a, b), c); }
-__device__ __forceinline__ float rows4_max_f32(float v) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float m = max2_f32(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
-  const uint32_t w = __builtin_bit_cast(uint32_t, m);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return max2_f32(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
-}
-__device__ __forceinline__ float rows4_sum_f32(float v) {
-  const uint32_t u = __builtin_bit_cast(uint32_t, v);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const float m = __builtin_bit_cast(float, (uint32_t)a[0]) + __builtin_bit_cast(float, (uint32_t)a[1]);
-  const uint32_t w = __builtin_bit_cast(uint32_t, m);
-  const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
 }
 
 // Register-staged attention, for the head widths whose tiles the load-to-LDS ring cannot take (rows under 128
@@ -657,31 +635,73 @@ static int attn_waves(int L, int heads_x_batch, int ring_bytes, int waves_per_cu
   return best < 0 ? 8 : best;
 }
 
-#ifndef TOMA_ATTN_QT
-#define TOMA_ATTN_QT 1   // query tiles per wave: 1 (any number of waves) or 2 (four waves)
-#endif
-// nw: waves per workgroup, 0 = chosen by attn_waves
+// Which kernel for 64- and 128-wide bf16 heads, and how many waves per workgroup.  Workgroups are placed `cap` to a CU
+// (registers: three waves per SIMD of the 16-query kernel, two of the 32-query one; LDS: two rings of 64-wide heads,
+// one of 128-wide ones) in rounds over the 256 CUs, and a round takes as long as its busiest SIMD: the microseconds per
+// 64-key tile below, by waves on that SIMD, fitted to sweeps of both kernels over 4 to 12 waves at 128 to 8192 tokens
+// and 5 to 80 heads.  The larger query tile is the cheaper one per query (1.1 against 1.3 us for 64 queries of a SIMD)
+// and the coarser one: 20 heads of 2048 tokens take 33.1 us with 11 waves of 16 queries and 34.7 with four of 32, of
+// 8192 tokens 461 and 376.  128-wide heads have registers for the 32-query kernel only.
+struct AttnPlan { bool narrow; int waves; };
+static AttnPlan plan_attn_pipe(int Lq, int heads_x_batch, int dh) {
+  AttnPlan best{dh < 128, 4};
+  float least = 0.f;
+  long best_wgs = 0;
+  auto consider = [&](bool narrow, int nw) {
+    const int per_simd = (nw + 3) / 4;
+    const int cap = dh >= 128 ? 1 : std::min(2, (narrow ? 3 : 2) / per_simd);
+    auto round = [&](long wgs_per_cu) -> float {
+      const long k = wgs_per_cu * per_simd;
+      if (k == 0) return 0.f;
+      if (dh >= 128) return nw == 4 ? 1.2f : nw <= 6 ? 1.5f : 1.68f;
+      if (narrow) return k == 1 ? 0.5f : k == 2 ? 0.65f : 0.88f;
+      return k == 1 ? 0.72f : 1.1f;
+    };
+    const int qb = (narrow ? 16 : 32) * nw;
+    const long wgs = (long)((Lq + qb - 1) / qb) * heads_x_batch, slots = 256L * cap;
+    const float cost = (float)(wgs / slots) * round(cap) + round((wgs % slots + 255) / 256);
+    // of equals, the one that spreads one workgroup per CU over the most CUs
+    const bool better = least == 0.f || cost < least || (cost == least && wgs <= 256 && (best_wgs > 256 || wgs > best_wgs));
+    if (better) { least = cost; best = AttnPlan{narrow, nw}; best_wgs = wgs; }
+  };
+  if (dh < 128) {
+    for (int nw : {4, 6, 8, 11, 12}) consider(true, nw);
+    consider(false, 4);
+  } else {
+    for (int nw = 4; nw <= 8; nw++) consider(false, nw);
+  }
+  return best;
+}
+
+// 1 / sqrt(head width) in units of the exponentials, which are powers of two.  The projection multiplies bf16 queries
+// by it before it rounds them (one rounding either way); fp32 scores are scaled in the exponent's multiply-add.
+static float attn_scale_log2(int dh) { return 1.4426950408889634f / sqrtf((float)dh); }
 template <typename T, int DH>
 static void launch_attn(const Shape &s, int Lq, int Lk, const T *Q, const T *K, const T *V, T *O, const float *Zs,
-                        T *Oe, hipStream_t st, int nw = 0) {
-  float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
+                        T *Oe, hipStream_t st) {
+  const float scale_log2 = sizeof(T) == 2 ? 1.0f : attn_scale_log2(DH);  // (bf16 queries come scaled)
   KernelTimer kt(K_ATTN, st);
-  // load-to-LDS pipeline when a row is at least eight packets and the ring of four tiles fits the LDS
-  constexpr int kRowPackets = DH * (int)sizeof(T) / 16;
-  constexpr int kRing = 4 * 2 * 64 * DH * (int)sizeof(T);
-  if constexpr (kRowPackets >= 8 && kRing <= 160 * 1024 - 4096) {
-    if (TOMA_ATTN_QT == 1) {
-      constexpr bool kWide = DH * sizeof(T) >= 256;  // three waves per SIMD fit the registers, else four
-      if (nw < (kWide ? 8 : 4) || nw > 12) nw = attn_waves(Lq, s.heads * s.B, kRing, kWide ? 12 : 16, kWide ? 8 : 4, kWide ? 2.3f : 2.0f);
-      dim3 grid((Lq + 16 * nw - 1) / (16 * nw) * s.heads * s.B);
-      hipLaunchKernelGGL((k_attn_async<T, DH, 1>), grid, dim3(64 * nw), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
-    } else {
-      dim3 grid((Lq + 127) / 128 * s.heads * s.B);
-      hipLaunchKernelGGL((k_attn_async<T, DH, 2>), grid, dim3(256), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
+  if constexpr (sizeof(T) == 2 && DH >= 64) {
+    const AttnPlan pl = plan_attn_pipe(Lq, s.heads * s.B, DH);
+    const int qb = (pl.narrow ? 16 : 32) * pl.waves;
+    const dim3 grid((Lq + qb - 1) / qb * s.heads * s.B), block(64 * pl.waves);
+    if constexpr (DH < 128) {
+      if (pl.narrow) {
+        hipLaunchKernelGGL((k_attn_pipe16<DH>), grid, block, 0, st, Q, K, V, O, Lq, Lk, s.heads, Zs, s.D, Oe);
+        return;
+      }
     }
+    hipLaunchKernelGGL((k_attn_pipe<DH>), grid, block, 0, st, Q, K, V, O, Lq, Lk, s.heads, Zs, s.D, Oe);
+  } else if constexpr (sizeof(T) == 4 && DH <= 64) {
+    // load-to-LDS ring of four tiles (those of 128-wide fp32 heads do not fit the LDS)
+    constexpr bool kWide = DH > 32;  // three waves per SIMD fit the registers, else four
+    constexpr int kRing = 4 * 2 * 64 * DH * (int)sizeof(T);
+    const int nw = attn_waves(Lq, s.heads * s.B, kRing, kWide ? 12 : 16, kWide ? 8 : 4, kWide ? 2.3f : 2.0f);
+    dim3 grid((Lq + 16 * nw - 1) / (16 * nw) * s.heads * s.B);
+    hipLaunchKernelGGL((k_attn_async<T, DH, 1>), grid, dim3(64 * nw), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
   } else {
     // one query tile per wave where two would leave fewer than two workgroups per CU (narrow rows only)
-    constexpr bool kNarrow = kRowPackets < 8;
+    constexpr bool kNarrow = DH * sizeof(T) < 128;
     const bool one = kNarrow && (long long)((Lq + 127) / 128) * s.heads * s.B < 512;
     const dim3 grid(one ? (Lq + 63) / 64 : (Lq + 127) / 128, s.heads, s.B);
     if (one)
@@ -704,6 +724,7 @@ static int attend_typed(const Shape &s, const void *Xm, const void *Xe, const vo
   p.B = s.B; p.D = s.D; p.Tx = s.T; p.L = s.L; p.C = s.C; p.H = s.heads; p.dh = s.head_dim; p.Kin = s.C;
   p.dh_sh = -1;
   for (int sh = 0; sh < 16; sh++) if ((1 << sh) == s.head_dim) p.dh_sh = sh;
+  p.scale0 = sizeof(T) == 2 ? attn_scale_log2(s.head_dim) : 1.0f;
   launch_gemm<T>(K_QKV, p, s.B * s.L, s.C, s.C, 3, st);
   T *Oh = Wo ? reinterpret_cast<T *>(ws + w.oh) : static_cast<T *>(O);
   switch (s.head_dim) {
@@ -741,12 +762,14 @@ static int cross_typed(const Shape &s, const void *U, const void *Ctx, int t_ctx
   pq.B = s.B; pq.D = s.L; pq.Tx = 0; pq.L = s.L; pq.C = s.C; pq.H = s.heads; pq.dh = s.head_dim; pq.Kin = s.C;
   pq.dh_sh = -1;
   for (int sh = 0; sh < 16; sh++) if ((1 << sh) == s.head_dim) pq.dh_sh = sh;
+  pq.scale0 = sizeof(T) == 2 ? attn_scale_log2(s.head_dim) : 1.0f;
   launch_gemm<T>(K_QKV, pq, s.B * s.L, s.C, s.C, 1, st);
   QkvPol<T> pk = pq;
   pk.Xm = static_cast<const T *>(Ctx);
   pk.W[0] = static_cast<const T *>(Wk); pk.W[1] = static_cast<const T *>(Wv);
   pk.out[0] = K; pk.out[1] = V;
   pk.D = t_ctx; pk.L = t_ctx; pk.Kin = c_ctx;
+  pk.scale0 = 1.0f;
   launch_gemm<T>(K_QKV, pk, s.B * t_ctx, s.C, c_ctx, 2, st);
   T *Oh = Wo ? reinterpret_cast<T *>(ws + w.oh) : static_cast<T *>(O);
   switch (s.head_dim) {

@@ -814,6 +814,31 @@ def test_attention_with_drifting_maxima(oracle, dtype, head_dim, order, B, heads
     _check_stage("O", O, ref, tg.TOL[dtype])
 
 
+@pytest.mark.parametrize("B,heads,head_dim,L", [
+    (2, 1, 64, 1), (2, 2, 64, 16), (2, 1, 64, 63), (2, 2, 64, 64), (2, 3, 64, 65), (2, 1, 64, 129), (2, 1, 64, 192),
+    (2, 5, 64, 240), (64, 8, 64, 1), (64, 8, 64, 97), (64, 8, 64, 128),
+    (2, 1, 128, 1), (2, 2, 128, 31), (2, 1, 128, 64), (2, 1, 128, 130), (2, 2, 128, 255)])
+def test_attention_wide_heads(oracle, B, heads, head_dim, L):
+    """bf16 heads of width 64 and 128: one, two and more key tiles with full and ragged ends, ragged blocks of queries,
+    and enough sample-heads (512) for the kernel of 32 queries per wave at width 64."""
+    C = head_dim * heads
+    w = synth.scaled(W["tiny"], name="wide", dtype="bf16", B=B, H=16, W=16, C=C, tile_h=16, tile_w=16, keep=L / 256,
+                     heads=heads, index=39)
+    assert w.D == L
+    print(f"[wide heads] {B} x {heads} heads of {head_dim}, {L} tokens", flush=True)
+    inp = synth.make_inputs(w)
+    dv = tg.Device(w, inp, 1)
+    Xm = synth.quantize(w, np.random.default_rng(40).standard_normal((B, L, C)).astype(np.float32))
+    Wts = [_f64(inp[k]) for k in ("Wq", "Wk", "Wv")]
+    _check_stage("O", dv.attend(Xm=Xm), oracle.attend(_f64(Xm), None, *Wts, heads=heads), tg.TOL["bf16"])
+
+
+@pytest.mark.parametrize("order", ["up", "down"])
+def test_attention_with_drifting_maxima_of_many_heads(oracle, order):
+    """The same drift with enough sample-heads for the kernel of 32 queries per wave."""
+    test_attention_with_drifting_maxima(oracle, "bf16", 64, order, 16, 8)
+
+
 @pytest.mark.parametrize("dtype,rows,C,hidden", [("f32", 200, 64, 256), ("bf16", 1000, 128, 512),
                                                   ("bf16", 333, 96, 160), ("bf16", 2 * 2048, 640, 2560),
                                                   # one to four K steps of 64, the last one half full
