@@ -129,6 +129,22 @@ inline bool weights_single_pass(int Nr, int Dr, int C, int batch, int elem_size)
   return single <= two;
 }
 
+// Does screening the weights (toma_screen.hip) pay?  In shader clocks: its three launches about 60000, 1500 per K step
+// (the exact products are bound by latency), and writing A and comparing 0.0022 per weight; the full product as priced
+// above.  Measured (us, full and screened): 128 x 128 grid 645 and 250; SDXL's first stage 45 and 44, a Flux block 59 and
+// 79 (long rows), fp32 rows of 1280 on a 32 x 32 grid 61 and 107.
+inline bool screen_pays(const Shape &s) {
+  const int es = s.dtype == TOMA_BF16 ? 2 : 4;
+  if (!gemm_async_fits(s.Nr, s.Dr, s.C, es)) return false;
+  const int batch = s.B * s.R;
+  double full;
+  if (weights_single_pass(s.Nr, s.Dr, s.C, batch, es))
+    full = 19000.0 + (double)(((long long)(s.Nr / 32) * batch + 255) / 256) * (s.C * es / 128) * s.Dr * 4.0;
+  else
+    full = 2.0 * plan_gemm_async(s.Nr, s.Dr, s.C, batch, es, false, false, false, 3).cost + 14000.0;
+  return full > 1.3 * (60000.0 + 1500.0 * (s.C * es / 128) + 0.0022 * batch * s.Nr * s.Dr);
+}
+
 int make_shape(const toma_desc *d, const toma_attn_desc *a, Shape *s);
 void plan_workspace(const Shape &s, Workspace *w);
 
@@ -150,6 +166,13 @@ size_t big_state_bytes(const Shape &s);
 // lse2 = the same as (largest logit, log of the sum)
 int launch_weight_stats(const Shape &s, const void *X, const int32_t *idx, float2 *stats, int stat_parts, float *lse,
                         float2 *lse2, int *slice, hipStream_t st);
+// Screening of a global merge's weights (toma_screen.hip): offsets of its scratch, which lies over the sections of
+// stages that are over or have not begun; act: one bit per 32 sources x 16 destinations, act_row bytes per 32 sources
+// order: (token, index) of every destination, region by region in grid order: the tiles are tiles of this order
+struct ScreenPlan { bool use; size_t q4, src, dst, order, act; int kc, act_row; };
+ScreenPlan plan_screen(const Shape &s, const Workspace &w);
+// marks the tiles of A that may hold a nonzero weight and fills A with zeros
+int launch_screen(const Shape &s, const ScreenPlan &p, const void *X, const int32_t *idx, void *A, char *ws, hipStream_t st);
 // occ: the occupancy map that travels with (A, Z), w.occ_bytes bytes (null iff the shape uses none).
 // launch_weights writes it along with A and Z; launch_occupancy rebuilds it from a stored A;
 // launch_merge / launch_unmerge read it.
@@ -192,7 +215,7 @@ int launch_mlp(int dtype, int rows, int C, int hidden, const void *In, const voi
 
 // Kernel identifiers of the profiling aid (toma_profile_*): one per kernel of the path.
 enum KernelId { K_LIMBS = 0, K_GRAM, K_GREEDY, K_WSTATS, K_LSE, K_WWRITE, K_ZSUM, K_MERGE, K_QKV, K_ATTN, K_PROJ,
-                K_SCALE, K_UNMERGE, K_SPLIT, K_MLP_UP, K_MLP_DOWN, K_OCC, K_PINV_EIG, K_PINV_APPLY, K_MERGE_FUSED, K_UNMERGE_FUSED, K_COUNT };
+                K_SCALE, K_UNMERGE, K_SPLIT, K_MLP_UP, K_MLP_DOWN, K_OCC, K_PINV_EIG, K_PINV_APPLY, K_MERGE_FUSED, K_UNMERGE_FUSED, K_WBOUNDS, K_COUNT };
 
 // Brackets one launch with HIP events on its stream while profiling is enabled; free otherwise.
 struct KernelTimer {

@@ -18,6 +18,7 @@
 #include "toma_gemm.h"
 #include "toma_internal.h"
 #include "toma_region.h"
+#include "toma_weights.h"
 
 namespace toma {
 
@@ -363,13 +364,8 @@ __device__ __forceinline__ void weights_one_pass_finish(f32x4 (&acc)[2][NJ], con
 // ---- weights in one pass ------------------------------------------------------------------------
 // One workgroup (8 waves) holds the logits of 32 sources against ALL Dr = 128 NJ destinations of the
 // merge region in its accumulators (wave w: destinations 16 NJ w .. 16 NJ (w + 1) - 1, 2 x NJ MFMA
-// tiles), so the softmax over destinations needs no second product: the statistics are exchanged
-// through LDS and A is written straight from the accumulators.
-// A K step is 128 bytes of every row: two 32-channel fragments (bf16) or one (fp32).  A destination
-// row is used by one wave only: every wave streams its own rows through a PRIVATE ring of LDS
-// stages (two MFMA tiles = 4 KiB each) with the load-to-LDS path, three stages ahead of the
-// products, and only its own s_waitcnt orders them.  The 32 source rows of a step are shared: four
-// waves fetch them into a double buffer and the workgroup meets once per K step.
+// tiles; weights_products), so the softmax over destinations needs no second product: the statistics
+// are exchanged through LDS and A is written straight from the accumulators.
 // Partial row sums of the STORED weights go to zpart[.][source tile] for k_zsum, as in the
 // two-pass path.
 template <typename T, int NJ>
@@ -377,121 +373,185 @@ __global__ __launch_bounds__(512) void k_weights_fused(const RegionView<T> v, co
                                                      T *__restrict__ A, int lda, float *__restrict__ zpart,
                                                      int zparts, uint8_t *__restrict__ occ, int occ_db, int occ_sb,
                                                      int tiles) {
-  constexpr int ES = (int)sizeof(T), EPS = 128 / ES;   // elements per K step
-  constexpr int EPP = 16 / ES;
-  constexpr int NH = ES == 2 ? 2 : 1;                  // fragments per row per K step
-  constexpr int JS = NJ < 2 ? 1 : 2;                   // MFMA tiles per stage
-  constexpr int SPS = NJ / JS;                         // stages per K step
-  constexpr int RS = 4;                                // ring stages per wave
-  constexpr int LPS = 2 * JS;                          // load instructions (1 KiB) per stage
-  constexpr int STAGE = JS * 16 * EPS;                 // elements per stage
-  __shared__ __align__(1024) T Bs[8][RS][2 * 16 * EPS];  // per wave ring (sized for two tiles per stage)
-  __shared__ __align__(1024) T As[2][32 * EPS];          // the step's 32 source rows, double buffered
+  __shared__ __align__(1024) WeightsLds<T> lds;
   __shared__ float red[8][32];       // per wave partial statistic of the 32 source rows
   __shared__ float rowstat[32];
-
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, g = lane >> 4, c = lane & 15;
   // Every workgroup of a region streams the region's whole set of destination rows: the workgroups an
   // XCD receives are consecutive source tiles of as few regions as possible, so that those rows stay
   // in its L2 (two samples' rows at SDXL's first stage would not fit one L2 together).
   const int work = xcd_remap(blockIdx.x, gridDim.x);
-  const int z = work / tiles, mt = work - z * tiles, b = z / v.R, rho = z % v.R;
-  const int m0 = mt * 32;
-  const T *Xb = v.X + (size_t)b * v.N * v.C;
-
-  // what this lane fetches of a 1 KiB chunk (8 rows x 128 bytes): row lane / 8, and the packet that
-  // the swizzle places at position lane % 8 of that row
-  const int l_row = lane >> 3;
-  const int l_pkt = ((lane & 7) ^ (l_row & 7)) * EPP;
-  // Element offsets (inside the sample) of the packets this lane fetches of its wave's destination
-  // rows, one per (stage of a K step, chunk): the same for every K step, so they stay in registers.
-  int roff[SPS][LPS];
-#pragma unroll
-  for (int q = 0; q < SPS; q++)
-#pragma unroll
-    for (int ch = 0; ch < LPS; ch++) {
-      int t = idx[(size_t)b * v.D + rho * v.Dr + w * 16 * NJ + 16 * (q * JS + (ch >> 1)) + 8 * (ch & 1) + l_row];
-      t = t < 0 ? 0 : (t >= v.N ? v.N - 1 : t);
-      roff[q][ch] = t * v.C + l_pkt;
-    }
-  // source rows: wave w < 4 fetches rows 8 w .. 8 w + 7 of every step
-  const T *a_src = Xb + (size_t)v.token(rho, m0 + 8 * (w & 3) + l_row) * v.C + l_pkt;
-  const int nsteps = v.C / EPS, U = nsteps * SPS;
-  // LDS byte addresses (scalar registers) of this wave's ring and of its part of the source rows
-  const uint32_t w_s = (uint32_t)__builtin_amdgcn_readfirstlane(w);
-  const uint32_t bs_lds = lds_addr_of(&Bs[0][0][0]) + w_s * (RS * 2 * 16 * EPS * ES);
-  const uint32_t as_lds = lds_addr_of(&As[0][0]) + (w_s & 3) * 1024;
-  auto issue_a = [&](int s) { load_to_lds16_at(a_src + s * EPS, as_lds + (uint32_t)(s & 1) * (32 * EPS * ES)); };
-  // stage u = s * SPS + q of the ring (q is a compile-time constant at every call)
-  auto issue_b = [&](int s, int q) {
-    const uint32_t dst = bs_lds + (uint32_t)((s * SPS + q) & (RS - 1)) * (2 * 16 * EPS * ES);
-    const T *src = Xb + s * EPS;
-#pragma unroll
-    for (int ch = 0; ch < LPS; ch++) load_to_lds16_at(src + roff[q][ch], dst + ch * 1024);
-  };
-  auto fence = [&]() { asm volatile("" ::: "memory"); };
-
+  const int z = work / tiles, mt = work - z * tiles, b = z / v.R, rho = z % v.R, w = threadIdx.x >> 6;
   f32x4 acc[2][NJ];
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int j = 0; j < NJ; j++) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-  // the index loads above have returned (their values were used): from here on vmcnt counts
-  // only ring loads
-  wait_vmcnt<0>();
-  if (w < 4) issue_a(0);
-#pragma unroll
-  for (int u = 0; u < RS - 1; u++)
-    if (u < U) issue_b(u / SPS, u % SPS);
-  wait_vmcnt<0>();
-  fence();
-  __builtin_amdgcn_s_barrier();
-  fence();
-
-  for (int s = 0; s < nsteps; s++) {
-    if (w < 4 && s + 1 < nsteps) issue_a(s + 1);
-    Frag<T> fa[2][NH];
-#pragma unroll
-    for (int i = 0; i < 2; i++)
-#pragma unroll
-      for (int h = 0; h < NH; h++) frag_load_kc_sw(fa[i][h], As[s & 1], 16 * i + c, 32 * h + 8 * g);
-#pragma unroll
-    for (int q = 0; q < SPS; q++) {
-      const int u = s * SPS + q;
-      if (u + RS - 1 < U) issue_b(s + (q + RS - 1) / SPS, (q + RS - 1) % SPS);
-      // this wave's loads of stage u are the oldest outstanding ones
-      const int younger = min(U - 1 - u, RS - 1);
-      if (younger >= 3) wait_vmcnt<3 * LPS>();
-      else if (younger == 2) wait_vmcnt<2 * LPS>();
-      else if (younger == 1) wait_vmcnt<LPS>();
-      else wait_vmcnt<0>();
-      fence();
-      const T *bt = Bs[w][u & (RS - 1)];
-#pragma unroll
-      for (int t = 0; t < JS; t++)
-#pragma unroll
-        for (int h = 0; h < NH; h++) {
-          Frag<T> fb;
-          frag_load_kc_sw(fb, bt, 16 * t + c, 32 * h + 8 * g);
-#pragma unroll
-          for (int i = 0; i < 2; i++) mma16(acc[i][q * JS + t], fa[i][h], fb);
-        }
-      // the fragment reads of this stage have returned before its slot is refilled (next trip)
-      __builtin_amdgcn_s_waitcnt(0xc07f);
-      fence();
-    }
-    // the next step's source rows have landed (they are older than the ring loads issued during a
-    // long step; a short step waits for them explicitly), and every wave is done with this step's
-    constexpr int kAfterA = SPS * LPS < (RS - 1) * LPS ? SPS * LPS : (RS - 1) * LPS;
-    if ((s + 1) * SPS + RS - 1 <= U) wait_vmcnt<kAfterA>();  // every stage of this step issued a refill after them
-    else wait_vmcnt<0>();                                     // (the last steps issue fewer)
-    fence();
-    __builtin_amdgcn_s_barrier();
-    fence();
-  }
-
+  const int32_t *ids = idx + (size_t)b * v.D + rho * v.Dr + w * 16 * NJ;
+  weights_products<T, NJ>(acc, lds, v, b, rho, 32 * mt, [=](int j, int r) {
+    const int t = ids[16 * j + r];
+    return t < 0 ? 0 : (t >= v.N ? v.N - 1 : t);
+  });
   weights_one_pass_finish<T, NJ>(acc, v, scale, A, lda, zpart, zparts, occ, occ_db, occ_sb, red, rowstat, z, mt);
+}
+
+// ---- weights of the marked tiles only ------------------------------------------------------------
+// A global merge whose tiles of 32 sources x 16 destinations were screened (toma_screen.hip; A is zero so far): the same
+// workgroup of 32 sources with the marked tiles in place of all destinations, 1 to 16 per wave as the list asks.
+// Where more than 128 are marked (a softmax that is not sharp), they are walked in chunks of 128 twice: statistics, then
+// weights.
+constexpr int kListMax = 2048;   // destination tiles (32768 destinations)
+template <typename T>
+__global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, const int2 *__restrict__ order, float scale,
+                                                      T *__restrict__ A, const uint8_t *__restrict__ act, int act_row,
+                                                      uint8_t *__restrict__ occ, int occ_db, int occ_sb, int tiles) {
+  __shared__ __align__(1024) WeightsLds<T> lds;
+  __shared__ float red[2][8][32];
+  __shared__ float row_max[32], row_sum[32];
+  __shared__ uint16_t list[kListMax];
+  __shared__ int list_n;
+  __shared__ uint8_t flags[kListMax / 8];
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int work = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = work / tiles, mt = work - b * tiles, m0 = 32 * mt;
+  const float k2 = scale * 1.44269504088896341f;
+  const int2 *ord = order + (size_t)b * v.Dr;  // (token, index) of the destinations in the screen's order
+
+  if (w == 0) {  // marked tiles in ascending order
+    const uint8_t *row = act + ((size_t)b * tiles + mt) * act_row;
+    int base = 0;
+    for (int i0 = 0; i0 < act_row; i0 += 64) {
+      uint32_t bits = i0 + lane < act_row ? row[i0 + lane] : 0;
+      int at = __popc(bits);
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(at, d, 64);
+        if (lane >= d) at += o;
+      }
+      const int total = __shfl(at, 63, 64);
+      at += base - __popc(bits);
+      for (; bits; bits &= bits - 1) list[at++] = (uint16_t)(8 * (i0 + lane) + __ffs(bits) - 1);
+      base += total;
+    }
+    if (lane == 0) list_n = base;
+  }
+  for (int i = tid; i < occ_db; i += 512) flags[i] = 0;
+  if (tid < 32) { row_max[tid] = -__builtin_inff(); row_sum[tid] = 0.f; }
+  __syncthreads();
+  const int na = __builtin_amdgcn_readfirstlane(list_n);
+
+  auto run = [&](auto nj_c) {
+    constexpr int NJ = decltype(nj_c)::value;
+    f32x4 acc[2][NJ];
+    auto products = [&](int e0) {
+      weights_products<T, NJ>(acc, lds, v, b, 0, m0, [&](int j, int r) {
+        return ord[min(16 * (int)list[min(e0 + 8 * j + w, na - 1)] + r, v.Dr - 1)].x;
+      });
+      // slots past the list's end and destinations past the last take no part
+#pragma unroll
+      for (int j = 0; j < NJ; j++)
+        if (!(e0 + 8 * j + w < na && 16 * (int)list[min(e0 + 8 * j + w, na - 1)] + c < v.Dr)) {
+#pragma unroll
+          for (int i = 0; i < 2; i++) acc[i][j] = (f32x4)(-__builtin_inff());
+        }
+    };
+    // largest product and sum of exponentials of every source row, joined with those of the chunks before
+    auto statistics = [&]() {
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          float m = -__builtin_inff();
+#pragma unroll
+          for (int j = 0; j < NJ; j++) m = fmaxf(m, acc[i][j][r]);
+          m = row16_max_f32(m);
+          if (c == 0) red[0][w][16 * i + 4 * g + r] = m;
+        }
+      __syncthreads();
+      float mk[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int at = 16 * i + 4 * g + r;
+          float m = row_max[at];
+#pragma unroll
+          for (int q = 0; q < 8; q++) m = fmaxf(m, red[0][q][at]);
+          mk[i][r] = m * k2;
+          float sum = 0.f;
+#pragma unroll
+          for (int j = 0; j < NJ; j++) sum += __builtin_amdgcn_exp2f(fmaf(acc[i][j][r], k2, -mk[i][r]));
+          sum = row16_sum_f32(sum);
+          if (c == 0) red[1][w][at] = sum;
+        }
+      __syncthreads();
+      if (tid < 32) {
+        float m = row_max[tid], sum = 0.f;
+        const float before = m;
+#pragma unroll
+        for (int q = 0; q < 8; q++) { m = fmaxf(m, red[0][q][tid]); sum += red[1][q][tid]; }  // (fixed order)
+        row_sum[tid] = (row_sum[tid] > 0.f ? row_sum[tid] * __builtin_amdgcn_exp2f((before - m) * k2) : 0.f) + sum;
+        row_max[tid] = m;
+      }
+      __syncthreads();
+    };
+    auto write = [&](int e0) {
+      float mk[2][4], inv[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          mk[i][r] = row_max[16 * i + 4 * g + r] * k2;
+          inv[i][r] = 1.0f / row_sum[16 * i + 4 * g + r];
+        }
+#pragma unroll
+      for (int j = 0; j < NJ; j++) {
+        const int e = e0 + 8 * j + w;
+        if (e >= na) break;  // (uniform)
+        const int at = 16 * __builtin_amdgcn_readfirstlane((int)list[e]) + c;
+        const int n = at < v.Dr ? ord[at].y : v.Dr;
+        alignas(16) T o[2][4];
+        bool nonzero = false;
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+          for (int r = 0; r < 4; r++) {
+            o[i][r] = from_f32<T>(__builtin_amdgcn_exp2f(fmaf(acc[i][j][r], k2, -mk[i][r])) * inv[i][r]);
+            nonzero |= to_f32(o[i][r]) != 0.f && (i == 0 || m0 + 16 < v.Nr);
+          }
+        if (nonzero && n < v.Dr) flags[n >> 7] = 1;  // (128 destinations; all write the same)
+        T *row = A + ((size_t)b * v.Dr + n) * v.Nr + m0;
+        if constexpr (sizeof(T) == 2) {
+          // (lanes g and g ^ 1 trade halves, as in the one-pass kernel: one 16-byte packet each)
+          const u32x2 own0 = *reinterpret_cast<u32x2 *>(o[0]), own1 = *reinterpret_cast<u32x2 *>(o[1]);
+          const bool odd = g & 1;
+          const u32x2 give = odd ? own0 : own1;
+          u32x2 got;
+          got[0] = (uint32_t)__shfl_xor((int)give[0], 16, 64);
+          got[1] = (uint32_t)__shfl_xor((int)give[1], 16, 64);
+          const u32x4 pk = odd ? (u32x4){got[0], got[1], own1[0], own1[1]} : (u32x4){own0[0], own0[1], got[0], got[1]};
+          if (n < v.Dr && (!odd || m0 + 16 < v.Nr)) *reinterpret_cast<u32x4 *>(row + (odd ? 16 + 4 * (g - 1) : 4 * g)) = pk;
+        } else {
+#pragma unroll
+          for (int i = 0; i < 2; i++)
+            if (n < v.Dr && m0 + 16 * i < v.Nr) *reinterpret_cast<u32x4 *>(row + 16 * i + 4 * g) = *reinterpret_cast<u32x4 *>(o[i]);
+        }
+      }
+    };
+    if (na <= 8 * NJ) {
+      products(0);
+      statistics();
+      write(0);
+    } else {
+      for (int e0 = 0; e0 < na; e0 += 8 * NJ) { products(e0); statistics(); }
+      for (int e0 = 0; e0 < na; e0 += 8 * NJ) { products(e0); write(e0); }
+    }
+  };
+  if (na > 64) run(std::integral_constant<int, 16>{});
+  else if (na > 32) run(std::integral_constant<int, 8>{});
+  else if (na > 16) run(std::integral_constant<int, 4>{});
+  else if (na > 8) run(std::integral_constant<int, 2>{});
+  else if (na > 0) run(std::integral_constant<int, 1>{});
+  if (occ) {
+    __syncthreads();
+    for (int i = tid; i < occ_db; i += 512) occ[((size_t)b * occ_db + i) * occ_sb + mt] = flags[i];
+  }
 }
 
 // ---- merge -------------------------------------------------------------------------------------
@@ -731,6 +791,20 @@ static int weights_typed(const Shape &s, const void *X, const int32_t *idx, void
   const int zr = s.B * s.D;
   // partial row sums of the stored weights, for k_zsum: not needed where the merge product makes Z
   float *zpart = w.z_in_merge ? nullptr : reinterpret_cast<float *>(ws + w.zpart);
+  const ScreenPlan screen = plan_screen(s, w);
+  if (screen.use) {
+    const int rc = launch_screen(s, screen, X, idx, A, ws, st);
+    if (rc != TOMA_OK) return rc;
+    const int tiles = (s.N + 31) / 32;
+    KernelTimer kt(K_WWRITE, st);
+    const RegionView<T> v = make_view<T>(s, X);
+    const int2 *order = reinterpret_cast<const int2 *>(ws + screen.order);
+    const uint8_t *act = reinterpret_cast<const uint8_t *>(ws + screen.act);
+    uint8_t *occ = w.occ_sb ? occ_out : nullptr;
+    hipLaunchKernelGGL((k_weights_sparse<T>), dim3(tiles * s.B), dim3(512), 0, st, v, order, s.scale, static_cast<T *>(A), act,
+                       screen.act_row, occ, w.occ_db, w.occ_sb, tiles);
+    return launch_status();
+  }
   if (weights_single_pass(s.Nr, s.Dr, s.C, batch, (int)sizeof(T))) {
     const RegionView<T> v = make_view<T>(s, X);
     const int tiles = s.Nr / 32;

@@ -11,7 +11,7 @@ namespace toma {
 static const char *const kNames[K_COUNT] = {"limbs", "gram", "greedy", "weights_stats", "lse", "weights_write",
                                             "zsum", "merge", "qkv", "attention", "proj", "scale_rows",
                                             "unmerge", "split_finish", "mlp_up", "mlp_down", "occupancy",
-                                            "pinv_eig", "pinv_apply", "merge_recompute", "unmerge_recompute"};
+                                            "pinv_eig", "pinv_apply", "merge_recompute", "unmerge_recompute", "weights_bounds"};
 struct Rec { int id; hipEvent_t a, b; };
 static std::mutex g_mu;
 static std::atomic<bool> g_on{false};
@@ -106,7 +106,7 @@ TOMA_API int toma_profile_map_product(const toma_desc *desc, int which, int32_t 
   plan_workspace(s, &w);
   const int es = s.dtype == TOMA_BF16 ? 2 : 4;
   if (which == 2) {  // the write pass of the two-pass weights: sources x destinations
-    if (weights_single_pass(s.Nr, s.Dr, s.C, s.B * s.R, es) || !gemm_async_fits(s.Nr, s.Dr, s.C, es)) return TOMA_ERR_UNSUPPORTED;
+    if (plan_screen(s, w).use || weights_single_pass(s.Nr, s.Dr, s.C, s.B * s.R, es) || !gemm_async_fits(s.Nr, s.Dr, s.C, es)) return TOMA_ERR_UNSUPPORTED;
     const GemmPlan pl = plan_gemm_async(s.Nr, s.Dr, s.C, s.B * s.R, es, false, false, false, 3);
     out3[0] = pl.bm; out3[1] = pl.bn; out3[2] = pl.nsplit;
     return TOMA_OK;

@@ -491,6 +491,78 @@ def test_merge_unmerge_skip_only_empty_blocks(oracle, dtype, tau, C, passes):
     _check_stage("Y", Y, oracle.unmerge(d, A_in, np.maximum(Z_ref, 1e-20), _f64(O)), tol)
 
 
+@pytest.mark.parametrize("dtype,grid,tile,d_loc,C,tau,how", [
+    ("bf16", (64, 80), (16, 16), 192, 256, 0.1, ""),         # D = 3840: whole tiles of 16 destinations
+    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, ""),          # blocks of 32 sources in two regions, D = 2556: a ragged last tile
+    ("f32", (64, 80), (16, 16), 192, 320, 0.1, ""),
+    ("bf16", (64, 80), (16, 16), 192, 256, 100.0, ""),       # no tile is empty: more than 128 per block, in chunks, twice
+    ("f32", (64, 80), (16, 16), 192, 320, 3.0, ""),          # some are
+    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "repeated"),  # destinations that repeat and lie outside their region
+    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "uneven"),    # zero, tiny and large tokens
+    ("f32", (32, 64), (8, 8), 48, 3072, 0.1, "")])           # the longest rows that are screened
+def test_screened_merge_weights(oracle, dtype, grid, tile, d_loc, C, tau, how):
+    """Weights of large global merges, whose tiles are screened by a 4-bit product first: A / Z, Z and merged tokens
+    against the oracle, and the block map by way of the unmerge."""
+    H, Wd = grid
+    th, tw = tile
+    w = synth.scaled(W["tiny"], name="screen", dtype=dtype, B=2, H=H, W=Wd, C=C, tile_h=th, tile_w=tw, keep=d_loc / (th * tw),
+                     heads=C // 32, tau=tau, index=43)
+    print(f"[screened weights] {dtype} grid {H}x{Wd} tile {th}x{tw} D={w.D} C={C} tau={tau} {how}", flush=True)
+    inp = synth.make_inputs(w)
+    rng = np.random.default_rng(44)
+    if how == "uneven":
+        X = np.array(inp["X"], dtype=np.float32)
+        X[:, ::97] *= 0.0
+        X[:, 5::101] *= 1e-20
+        X[:, 7::103] *= 3.0
+        inp["X"] = synth.quantize(w, X)
+    X = _f64(inp["X"])
+    # (a weight's exponent carries the fp32 rounding of logits of up to |x|^2 / tau: eight roundings of the largest)
+    tol = max(tg.TOL[dtype], 8 * 2.0 ** -24 * (X ** 2).sum(axis=-1).max() / tau)
+    d = tg.oracle_desc(oracle, w, 1)
+    P = w.D // d_loc
+    if how == "repeated":
+        idx = rng.integers(0, w.N, size=(2, P, d_loc)).astype(np.int32)
+        idx[:, :, 1::2] = idx[:, :, ::2][:, :, :d_loc // 2]
+    else:  # random destinations of every region (the selection itself is tested elsewhere)
+        _, _, tokens = oracle.region_map(H, Wd, th, tw)
+        idx = np.stack([np.stack([rng.permutation(tokens[p])[:d_loc] for p in range(P)]) for _ in range(2)]).astype(np.int32)
+    A_ref, Z_ref, _ = oracle.merge_weights(d, X, idx)
+    Xm_ref = oracle.merge(d, X, A_ref, Z_ref)
+    dv = tg.Device(w, inp, 1)
+    tb.toma_profile_enable(True)
+    try:
+        tb.toma_profile_read("weights_bounds")
+        A, Z, Xm = dv.merge(idx=idx)
+        screened, _ = tb.toma_profile_read("weights_bounds")
+    finally:
+        tb.toma_profile_enable(False)
+    assert screened == 1
+    _check_stage("A~", A / np.maximum(Z, 1e-20).reshape(w.B, 1, -1, 1), A_ref / np.maximum(Z_ref, 1e-20).reshape(w.B, 1, -1, 1), tol)
+    _check_stage("Z", Z, Z_ref, tol)
+    _check_stage("Xm", Xm, Xm_ref, tol)
+    assert np.allclose(A.sum(axis=2), 1.0, atol=3 * tol)
+    O = synth.quantize(w, rng.standard_normal((w.B, w.D, w.C)).astype(np.float32))
+    _check_stage("Y", dv.unmerge(O=O), oracle.unmerge(d, _f64(A), np.maximum(_f64(Z), 1e-20), _f64(O)), tol)
+
+
+def test_screened_merge_weights_of_values_that_are_not_finite():
+    """A token that holds a NaN or an infinity, and is no destination, leaves every other token's weights as they are."""
+    w = synth.scaled(W["tiny"], name="screen", dtype="bf16", B=1, H=72, W=72, C=704, tile_h=12, tile_w=12, keep=71 / 144,
+                     heads=22, index=45)
+    inp = synth.make_inputs(w)
+    dv = tg.Device(w, inp, 1)
+    dv.select()
+    A0, _, _ = dv.merge()
+    idx = dv.idx.cpu().numpy().reshape(-1)
+    free = np.setdiff1d(np.arange(w.N), idx)[[3, 400]]
+    dv.X[0, int(free[0]), 17] = float("nan")
+    dv.X[0, int(free[1]), 33] = float("inf")
+    A1, _, _ = dv.merge(idx=dv.idx.cpu().numpy())
+    keep = ~np.isin(np.arange(w.N), free)
+    assert np.array_equal(A0[0, 0][:, keep], A1[0, 0][:, keep])
+
+
 def _crafted_weights(rng, B, D, N, case):
     """Sparse weights [B, D, N] with the sources in the order the library stores them: one to three
     destinations per source, all inside the source's own 128-destination block, plus what the case
