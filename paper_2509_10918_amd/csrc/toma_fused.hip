@@ -58,19 +58,48 @@ template <typename T, bool UNMERGE> struct FusedPol {
   __device__ __forceinline__ const T *v_row(int b, int rho, int n) const {
     return UNMERGE ? Os + ((size_t)b * os_rows + rho * v.Dr + n) * v.C : k_row(b, rho, n);
   }
-  // may any weight between queries [m0, m1) and keys [n0, n1) be nonzero?
-  __device__ __forceinline__ bool tile_active(int z, int m0, int m1, int n0, int n1) const {
-    const int s0 = UNMERGE ? m0 : n0, s1 = UNMERGE ? m1 : n1;  // sources
-    const int j0 = UNMERGE ? n0 : m0, j1 = UNMERGE ? n1 : m1;  // destinations
-    const int p0 = j0 / slice, p1 = min((j1 - 1) / slice, parts - 1);
-    for (int s = s0; s < s1; s++) {
-      const float2 ml = lse[(size_t)z * v.Nr + s];
-      const float l = ml.x + ml.y;
-      const float2 *row = stats + ((size_t)z * v.Nr + s) * parts;
-      for (int q = p0; q <= p1; q++)
-        if (!(row[q].x - l < -kFusedEmptyGap)) return true;
+  // may source s have a nonzero weight in slice q of the destinations?
+  __device__ __forceinline__ bool active(int z, int s, int q) const {
+    const float2 ml = lse[(size_t)z * v.Nr + s];
+    return !(stats[((size_t)z * v.Nr + s) * parts + q].x - (ml.x + ml.y) < -kFusedEmptyGap);
+  }
+  // The key tiles that may hold a nonzero weight for queries [m0, m1), compacted into klist by the whole workgroup
+  // (512 threads); returns their number.  Every thread asks about sources of its own, so that the loads are independent
+  // (one lane per tile, source after source: 18 us for 4096 sources).
+  __device__ __forceinline__ int list_tiles(int z, int m0, int m1, uint32_t *mark, uint16_t *klist, int *klist_n) const {
+    const int tid = threadIdx.x, lane = tid & 63, ntiles = (nk() + kFusedKeys - 1) / kFusedKeys;
+    for (int i = tid; i < (ntiles + 31) / 32; i += 512) mark[i] = 0;
+    __syncthreads();
+    auto set = [&](int t) { atomicOr(&mark[t >> 5], 1u << (t & 31)); };
+    if (UNMERGE) {
+      const int used = min((v.Dr + slice - 1) / slice, parts);
+      for (int e = tid; e < (m1 - m0) * used; e += 512) {
+        const int s = e / used, q = e - s * used;
+        if (active(z, m0 + s, q))
+          for (int t = q * slice / kFusedKeys; t <= min((q + 1) * slice - 1, v.Dr - 1) / kFusedKeys; t++) set(t);
+      }
+    } else {
+      const int p0 = m0 / slice, p1 = min((m1 - 1) / slice, parts - 1);
+      for (int s = tid; s < v.Nr; s += 512) {
+        bool any = false;
+        for (int q = p0; q <= p1; q++) any |= active(z, s, q);
+        if (any) set(s / kFusedKeys);
+      }
     }
-    return false;
+    __syncthreads();
+    if (tid < 64) {
+      int count = 0;
+      for (int t0 = 0; t0 < ntiles; t0 += 64) {
+        const int t = t0 + lane;
+        const bool act = t < ntiles && ((mark[t >> 5] >> (t & 31)) & 1u);
+        const uint64_t mask = __ballot(act);
+        if (act) klist[count + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)t;
+        count += __popcll(mask);
+      }
+      if (lane == 0) *klist_n = count;
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(*klist_n);
   }
 };
 
@@ -98,6 +127,7 @@ __global__ __launch_bounds__(512) void k_fused(const FusedPol<T, UNMERGE> pol) {
   __shared__ __align__(16) float Sp[8][256];          // partial logit tiles, [wave][4 r][64 lanes]
   __shared__ __align__(16) T Pt[BQ * LDP];
   __shared__ uint16_t klist[kFusedMaxTiles];
+  __shared__ uint32_t mark[kFusedMaxTiles / 32];
   __shared__ int klist_n;
 
   const RegionView<T> &v = pol.v;
@@ -105,22 +135,8 @@ __global__ __launch_bounds__(512) void k_fused(const FusedPol<T, UNMERGE> pol) {
   const int z = blockIdx.y, b = z / v.R, rho = z % v.R;
   const int m0 = blockIdx.x * BQ, NQ = pol.nq(), NK = pol.nk(), C = v.C;
   const int m1 = min(m0 + BQ, NQ);
-  const int ntiles = (NK + kFusedKeys - 1) / kFusedKeys;
 
-  // ---- key tiles that may hold a weight for these queries ----
-  if (w == 0) {
-    int count = 0;
-    for (int t0 = 0; t0 < ntiles; t0 += 64) {
-      const int kt = t0 + lane;
-      const bool act = kt < ntiles && pol.tile_active(z, m0, m1, kt * kFusedKeys, min((kt + 1) * kFusedKeys, NK));
-      const uint64_t mask = __ballot(act);
-      if (act) klist[count + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)kt;
-      count += __popcll(mask);
-    }
-    if (lane == 0) klist_n = count;
-  }
-  __syncthreads();
-  const int nlist = klist_n;
+  const int nlist = pol.list_tiles(z, m0, m1, mark, klist, &klist_n);  // key tiles that may hold a weight for these queries
 
   // this wave's part of the logits: tile (rt, ct) of the 16 RT x 32 block, channel steps [ks0, ks1)
   const int tile = w % NT, rt = tile >> 1, ct = tile & 1, sp = w / NT;
@@ -273,6 +289,225 @@ __global__ __launch_bounds__(512) void k_fused(const FusedPol<T, UNMERGE> pol) {
   }
 }
 
+// The same for bf16 rows of up to 640 channels, whose 32 keys fit a slot of LDS whole: every row of a tile is read from
+// memory once, coalesced, by the load-to-LDS path, while the tile before is worked on (in k_fused the logits' operands
+// and the values of a tile are requested when they are needed, three latencies per tile: SDXL's first stage 109 us for
+// the merge and 110 for the unmerge; 39 and 37 us so, list of tiles included).
+// Merge: keys and values are the same rows, two slots in turn.  Unmerge: keys are tokens, values rows of O / Z; three
+// slots in turn, K of a tile, V of it, K of the next, ...
+// A slot holds [32 rows][C / 8 packets of 16 bytes], packet p of a row at p ^ swizzle(row): the logits read 16 rows, one
+// packet each, the values four rows x 32 bytes per 16 lanes.
+template <bool UNMERGE, int RT, int CTC>
+__global__ __launch_bounds__(512) void k_fused_ring(const FusedPol<bf16_t, UNMERGE> pol) {
+  typedef bf16_t T;
+  constexpr int BQ = 16 * RT, NT = 2 * RT, NSPLIT = 8 / NT;
+  constexpr int SLOTS = UNMERGE ? 3 : 2, SLOT = kFusedKeys * 128 * CTC;  // elements
+  constexpr int LDP = kFusedKeys + 8;
+  constexpr int KQ = (4 * CTC + NSPLIT - 1) / NSPLIT;  // 32-channel steps of a wave's logits, at most
+  constexpr int TOKS = 64;                             // listed tiles whose tokens (unmerge) or statistics are at hand
+  __shared__ __align__(1024) T Sl[SLOTS][SLOT];
+  __shared__ __align__(16) float Sp[8][256];
+  __shared__ __align__(16) T Pt[BQ * LDP];
+  __shared__ uint16_t klist[kFusedMaxTiles];
+  __shared__ uint32_t mark[kFusedMaxTiles / 32];
+  __shared__ int klist_n;
+  __shared__ int toks[UNMERGE ? TOKS * kFusedKeys : 1];
+  __shared__ __align__(16) float2 bias[UNMERGE ? 1 : TOKS * kFusedKeys];
+  __shared__ float zrow[BQ];
+
+  const RegionView<T> &v = pol.v;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int z = blockIdx.y, b = z / v.R, rho = z % v.R;
+  const int m0 = blockIdx.x * BQ, NQ = pol.nq(), NK = pol.nk(), C = v.C;
+  const int m1 = min(m0 + BQ, NQ);
+
+  // this wave's part of the logits: tile (rt, ct) of the 16 RT x 32 block, channel steps [ks0, ks1); its queries' share
+  const int tile = w % NT, rt = tile >> 1, ct = tile & 1, sp = w / NT;
+  const int ksteps = C / 32, ks0 = ksteps * sp / NSPLIT, ks1 = ksteps * (sp + 1) / NSPLIT;
+  Frag<T> fq[KQ];
+  {
+    const T *q_ptr = pol.q_row(b, rho, min(m0 + 16 * rt + c, NQ - 1)) + 8 * g;
+#pragma unroll
+    for (int k = 0; k < KQ; k++) frag_load_global(fq[k], q_ptr + 32 * min(ks0 + k, ksteps - 1));
+  }
+  constexpr int ITEMS = BQ * kFusedKeys / 4;
+  const bool maker = tid < ITEMS;
+  const int pm = tid / 8, pk0 = (tid % 8) * 4;
+  float2 bias_q = make_float2(0.f, 0.f);
+  if (UNMERGE && maker && m0 + pm < NQ) bias_q = pol.lse[(size_t)z * v.Nr + m0 + pm];
+  float zsum = 0.f;
+
+  // ---- loads: wave w takes the 1 KiB pieces w CTC .. w CTC + CTC - 1 of a slot (the last one again past the end) ----
+  const int ppr = C / 8, pieces = ppr / 2;
+  const int span = min(ppr & -ppr, 16);  // the swizzle stays inside groups of so many packets
+  auto swz = [&](int row) { return (((row >> 2) & 1) | ((row & 1) << 1) | (((row >> 1) & 1) << 2) | (((row >> 3) & 1) << 3)) & (span - 1); };
+  int l_row[CTC], l_off[CTC];
+  uint32_t l_lds[CTC];
+#pragma unroll
+  for (int t = 0; t < CTC; t++) {
+    const int piece = min(w * CTC + t, pieces - 1), at = piece * 64 + lane;
+    l_row[t] = at / ppr;
+    l_off[t] = ((at - l_row[t] * ppr) ^ swz(l_row[t])) * 8;
+    l_lds[t] = lds_addr_of(&Sl[0][0]) + (uint32_t)piece * 1024;
+  }
+  const T *Xb = v.X + (size_t)b * v.N * C;
+  auto issue_keys = [&](int it, int slot) {  // `it`: position in the list
+    const int n0 = (int)klist[it] * kFusedKeys;
+#pragma unroll
+    for (int t = 0; t < CTC; t++) {
+      int tok;
+      if constexpr (UNMERGE) tok = toks[(it & (TOKS - 1)) * kFusedKeys + l_row[t]];
+      else tok = v.token(rho, min(n0 + l_row[t], NK - 1));
+      load_to_lds16_at(Xb + (size_t)tok * C + l_off[t], l_lds[t] + (uint32_t)(slot * SLOT * 2));
+    }
+  };
+  auto issue_values = [&](int it, int slot) {
+    const int n0 = (int)klist[it] * kFusedKeys;
+    const T *base = pol.Os + ((size_t)b * pol.os_rows + rho * v.Dr) * C;
+#pragma unroll
+    for (int t = 0; t < CTC; t++)
+      load_to_lds16_at(base + (size_t)min(n0 + l_row[t], NK - 1) * C + l_off[t], l_lds[t] + (uint32_t)(slot * SLOT * 2));
+  };
+  // what the next TOKS listed tiles need of memory besides their rows (every wave has used what is at hand; loads inside
+  // the loop would wait for the rows in flight)
+  auto refill = [&](int it0, int nlist) {
+    __syncthreads();
+    for (int e = tid; e < min(nlist - it0, TOKS) * kFusedKeys; e += 512) {
+      const int n = min((int)klist[it0 + e / kFusedKeys] * kFusedKeys + e % kFusedKeys, NK - 1);
+      if constexpr (UNMERGE) toks[e] = pol.dest_token(b, rho, n);
+      else bias[e] = pol.lse[(size_t)z * v.Nr + n];
+    }
+    __syncthreads();
+  };
+  auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  f32x4 acc[RT][CTC];
+#pragma unroll
+  for (int i = 0; i < RT; i++)
+#pragma unroll
+    for (int j = 0; j < CTC; j++) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+  const int nlist = pol.list_tiles(z, m0, m1, mark, klist, &klist_n);  // key tiles that may hold a weight for these queries
+  wait_vmcnt<0>();
+  if (nlist > 0) {
+    refill(0, nlist);
+    issue_keys(0, 0);
+    if (UNMERGE) issue_values(0, 1);
+  }
+  int ks = 0, vs = UNMERGE ? 1 : 0;  // slots of this tile's keys and values
+  for (int it = 0; it < nlist; it++) {
+    const int n0 = (int)klist[it] * kFusedKeys;
+    float2 bias_k[4];
+    if constexpr (!UNMERGE) {
+#pragma unroll
+      for (int u = 0; u < 4; u++) bias_k[u] = bias[(it & (TOKS - 1)) * kFusedKeys + pk0 + u];
+    }
+    // the keys have landed; every wave is done with the tile before
+    if (UNMERGE) wait_vmcnt<CTC>(); else wait_vmcnt<0>();
+    meet();
+    const int ks_next = UNMERGE ? (vs == 2 ? 0 : vs + 1) : ks ^ 1;
+    if (it + 1 < nlist) {
+      if (((it + 1) & (TOKS - 1)) == 0) refill(it + 1, nlist);
+      issue_keys(it + 1, ks_next);
+    }
+    // ---- 1. logits of this wave's tile over its channel slice ----
+    {
+      const int row = 16 * ct + c;
+      const T *kr = Sl[ks] + row * C;
+      f32x4 sacc = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < KQ; k++) {
+        if (ks0 + k < ks1) {  // (uniform)
+          Frag<T> fb;
+          fb.v = *reinterpret_cast<const bf16x8 *>(kr + ((4 * (ks0 + k) + g) ^ swz(row)) * 8);
+          mma16(sacc, fq[k], fb);  // lane: key column c, query rows 4 g + r
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; r++) Sp[w][64 * r + lane] = sacc[r];
+    }
+    meet();  // the logits are in LDS; every wave is done with the keys
+    if (UNMERGE && it + 1 < nlist) issue_values(it + 1, ks);
+    // ---- 2. weights: p = exp(scale * logit - lse), rounded to the element type ----
+    if (maker) {
+      const int prt = pm >> 4, pr = pm & 15, pct = pk0 >> 4, pc = pk0 & 15;
+      f32x4 lg = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < NSPLIT; q++)
+        lg += *reinterpret_cast<const f32x4 *>(&Sp[q * NT + 2 * prt + pct][64 * (pr & 3) + 16 * (pr >> 2) + pc]);
+      alignas(8) T o[4];
+      float rowsum = 0.f;
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int n = n0 + pk0 + u;
+        const float bm = UNMERGE ? bias_q.x : bias_k[u].x, bl = UNMERGE ? bias_q.y : bias_k[u].y;
+        const float p = (n < NK && m0 + pm < NQ) ? __expf(__builtin_fmaf(lg[u], pol.scale, -bm) - bl) : 0.f;
+        o[u] = from_f32<T>(p);
+        rowsum += to_f32(o[u]);
+      }
+      *reinterpret_cast<u32x2 *>(&Pt[pm * LDP + pk0]) = *reinterpret_cast<u32x2 *>(o);
+      if (!UNMERGE) {
+        rowsum += __shfl_xor(rowsum, 1, 64);
+        rowsum += __shfl_xor(rowsum, 2, 64);
+        rowsum += __shfl_xor(rowsum, 4, 64);
+        zsum += rowsum;
+      }
+    }
+    if (UNMERGE) {  // the values have landed (behind them: the next tile's keys and values)
+      if (it + 1 < nlist) wait_vmcnt<2 * CTC>(); else wait_vmcnt<0>();
+    }
+    meet();  // the weights are in LDS
+    // ---- 3. out^T += V^T P^T ----
+    Frag<T> fp[RT];
+#pragma unroll
+    for (int i = 0; i < RT; i++) frag_load_kc(fp[i], &Pt[(16 * i + c) * LDP + 8 * g]);
+#pragma unroll
+    for (int j = 0; j < CTC; j++) {
+      const int col = 16 * (w * CTC + j);
+      if (col < C) {
+        typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const int ra = 8 * g + (c >> 2), rb = ra + 4, cc = col + 4 * (c & 3);
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(Sl[vs] + ra * C + ((cc >> 3) ^ swz(ra)) * 8 + (cc & 7)));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(Sl[vs] + rb * C + ((cc >> 3) ^ swz(rb)) * 8 + (cc & 7)));
+        const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        Frag<T> fv;
+        fv.v = __builtin_bit_cast(bf16x8, both);
+#pragma unroll
+        for (int i = 0; i < RT; i++) mma16(acc[i][j], fv, fp[i]);  // lane: query c, channels 4 g + r
+      }
+    }
+    if constexpr (UNMERGE) {
+      vs = ks;       // (the next tile's values went where this tile's keys were)
+      ks = ks_next;
+    } else {
+      ks = vs = ks_next;
+    }
+  }
+
+  // ---- epilogue: lane holds, of query 16 i + c, the channels 16 (w CTC + j) + 4 g + r ----
+  if (!UNMERGE) {
+    if (maker && (tid & 7) == 0) {
+      zrow[pm] = zsum;
+      if (m0 + pm < NQ) pol.Z[(size_t)b * v.D + rho * v.Dr + m0 + pm] = zsum;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < RT; i++) {
+    const int m = m0 + 16 * i + c;
+    if (m >= NQ) continue;
+    const float sc = UNMERGE ? 1.0f : 1.0f / fmaxf(zrow[16 * i + c], 1e-20f);
+    T *dst = UNMERGE ? pol.out + ((size_t)b * v.N + v.token(rho, m)) * C : pol.out + ((size_t)b * v.D + rho * v.Dr + m) * C;
+#pragma unroll
+    for (int j = 0; j < CTC; j++) {
+      const int col = 16 * (w * CTC + j) + 4 * g;
+      if (col < C) store4<T>(dst + col, acc[i][j] * sc);
+    }
+  }
+}
+
 // Shapes the kernel is built for: (RT, CTC, NCH) by channel width, accumulators <= 96 registers.
 template <typename T, bool UNMERGE>
 static int launch_fused(const Shape &s, const FusedPol<T, UNMERGE> &pol, int kernel_id, hipStream_t st) {
@@ -297,7 +532,25 @@ static int launch_fused(const Shape &s, const FusedPol<T, UNMERGE> &pol, int ker
   }
   // (chunks of the value tile: two of them, 32 rows each, have to fit the LDS next to the rest)
   if constexpr (sizeof(T) == 2) {
-    if (s.C <= 128) { TOMA_FUSED_BY_RT(1) }
+    // rows of up to 640 channels fit the ring (a multiple of 64 channels: whole 1 KiB pieces of a slot)
+    if (s.C <= 640 && s.C % 64 == 0) {
+#define TOMA_RING(RT, CTC) \
+  hipLaunchKernelGGL((k_fused_ring<UNMERGE, RT, CTC>), dim3((NQ + 16 * RT - 1) / (16 * RT), s.B * s.R), dim3(512), 0, st, pol)
+#define TOMA_RING_BY_RT(CTC)              \
+  switch (rt_for(4)) {                    \
+    case 4: TOMA_RING(4, CTC); break;     \
+    case 2: TOMA_RING(2, CTC); break;     \
+    default: TOMA_RING(1, CTC); break;    \
+  }
+      if (s.C <= 128) { TOMA_RING_BY_RT(1) }
+      else if (s.C <= 256) { TOMA_RING_BY_RT(2) }
+      else if (s.C <= 384) { TOMA_RING_BY_RT(3) }
+      else if (rt_for(2) == 2) TOMA_RING(2, 5);  // (four query tiles of 640 channels spill)
+      else TOMA_RING(1, 5);
+#undef TOMA_RING_BY_RT
+#undef TOMA_RING
+    }
+    else if (s.C <= 128) { TOMA_FUSED_BY_RT(1) }
     else if (s.C <= 256) { TOMA_FUSED_BY_RT(2) }
     else if (s.C <= 640) { TOMA_FUSED_BY_RT(5) }
     else if (s.C <= 1280) { if (rt_for(2) == 2) TOMA_FUSED_LAUNCH(2, 5, 2); else TOMA_FUSED_LAUNCH(1, 5, 2); }

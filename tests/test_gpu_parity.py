@@ -1266,6 +1266,36 @@ def test_recomputed_weights_skip_only_empty_tiles(oracle, dtype, tau, C):
     _check_stage("Y", dv.unmerge_recompute(O=O_in), oracle.unmerge(d, A_ref, Z_ref, _f64(O_in)), tol)
 
 
+@pytest.mark.parametrize("grid,tile,d_loc,B,C,tau,tile_local", [
+    ((16, 16), (8, 8), 5, 1, 64, 1.0, True),        # a ragged tile of queries and of keys
+    ((24, 40), (6, 8), 48, 2, 192, 100.0, True),    # 48 keys: a tile and a half
+    ((40, 24), (8, 8), 33, 1, 320, 3.0, False),
+    ((32, 32), (16, 16), 100, 1, 384, 0.1, False),
+    ((64, 96), (16, 16), 200, 1, 64, 100.0, False),  # 150 tiles of destinations and 192 of sources, all of them listed
+    ((64, 64), (16, 16), 128, 3, 576, 0.5, False),   # 192 and 384 workgroups: one and two tiles of queries each
+    ((32, 48), (8, 8), 32, 1, 640, 0.3, True)])
+def test_recomputed_weights_of_narrow_rows(oracle, grid, tile, d_loc, B, C, tau, tile_local):
+    """bf16 rows of up to 640 channels, whose tiles of 32 keys go through LDS whole: merge and unmerge over the widths the
+    kernel is instantiated for, ragged ends, and more listed tiles than it keeps tokens at hand for."""
+    H, Wd = grid
+    w = synth.scaled(W["tiny"], name="rcn", dtype="bf16", B=B, H=H, W=Wd, C=C, tile_h=tile[0], tile_w=tile[1],
+                     keep=d_loc / (tile[0] * tile[1]), heads=C // 64, tau=tau, index=47)
+    print(f"[recompute narrow] grid {H}x{Wd} tile {tile} D={w.D} C={C} tau={tau} local={tile_local}", flush=True)
+    R = w.P if tile_local else 1
+    inp = synth.make_inputs(w)
+    tol = tg.TOL["bf16"]
+    X = _f64(inp["X"])
+    d = tg.oracle_desc(oracle, w, R)
+    idx, _, _ = oracle.select(d, X)
+    A_ref, Z_ref, _ = oracle.merge_weights(d, X, idx)
+    dv = tg.Device(w, inp, R)
+    Z, Xm = dv.merge_recompute(idx=idx)
+    _check_stage("Z", Z, Z_ref, tol)
+    _check_stage("Xm", Xm, oracle.merge(d, X, A_ref, Z_ref), tol)
+    O_in = synth.quantize(w, np.random.default_rng(48).standard_normal((w.B, w.D, w.C)).astype(np.float32))
+    _check_stage("Y", dv.unmerge_recompute(O=O_in), oracle.unmerge(d, A_ref, Z_ref, _f64(O_in)), tol)
+
+
 def test_binding_reports_errors_on_device():
     w, = (W["tiny"],)
     inp = synth.make_inputs(w)
