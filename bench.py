@@ -87,6 +87,12 @@ def kernel_work(w, R, esize, exec_frac=None, int8_gram=False):
                           else dict(bound=mm, amount=f["weights"],
                                     limit="L2 to CU bandwidth: every 32-source workgroup streams all destination rows "
                                           "(with the products or the loads taken out the loop takes 30 / 21 of its 35 us)")),
+        # screened weights: exact logits with the destinations of a source's own region, and the rows in 4 bits (the
+        # screen itself runs as weights_stats and leaves zeros in A; the exact tiles as weights_write)
+        "weights_bounds": dict(bound=mm, amount=2 * w.B * w.N * w.d_loc * w.C, limit="a chain of dependent loads"),
+        # one kernel per small merge region: logits (repeated per slice of the channels: not counted), softmax, merge
+        "local_merge": dict(bound=mm, amount=f["weights"] + f["merge"],
+                            limit="a chain of K steps per workgroup, each a wait, a barrier and a few products"),
         "zsum": dict(bound="hbm", amount=w.B * w.D * 8, limit="launch latency"),
         "merge": dict(bound=mm, amount=f["merge"] * ef.get("merge", 1.0), equiv=f["merge"]),
         "qkv": dict(bound=mm, amount=f["qkv"]),

@@ -105,6 +105,15 @@ void plan_workspace(const Shape &s, Workspace *w) {
   w->big_state = w->big + big_state_bytes(s) <= w->total;  // (always: stats and its like in fcache take 32 bytes per token)
 }
 
+// Fresh weights and the merge with them: one kernel where a merge region is small enough.
+static int weights_and_merge(const Shape &s, const void *X, const int32_t *idx, void *A, float *Z, uint8_t *occ, void *Xm,
+                             char *ws, const Workspace &w, hipStream_t st) {
+  if (w.occ_sb == 0 && local_merge_fits(s)) return launch_local_merge(s, X, idx, A, Z, Xm, st);
+  const int rc = launch_weights(s, X, idx, A, Z, occ, ws, w, st);
+  if (rc != TOMA_OK) return rc;
+  return launch_merge(s, X, A, Z, true, occ, Xm, ws, w, st);
+}
+
 static bool misaligned(const void *p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }
 
 // Shared prologue of every call: shape, workspace size and alignment.
@@ -242,9 +251,7 @@ TOMA_API int toma_merge(const toma_desc *desc, const void *X, const int32_t *idx
   if (rc != TOMA_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   uint8_t *occ = static_cast<uint8_t *>(amap);
-  rc = launch_weights(s, X, idx, A, Z, occ, static_cast<char *>(ws), w, st);
-  if (rc != TOMA_OK) return rc;
-  return launch_merge(s, X, A, Z, true, occ, Xm, static_cast<char *>(ws), w, st);
+  return weights_and_merge(s, X, idx, A, Z, occ, Xm, static_cast<char *>(ws), w, st);
 }
 
 TOMA_API int toma_merge_cached(const toma_desc *desc, const void *X, const void *A, const float *Z,
@@ -392,11 +399,8 @@ TOMA_API int toma_layer(const toma_desc *desc, const toma_attn_desc *attn, uint3
   if (recompute) {  // no A: the weights are recomputed inside the merge and again inside the unmerge
     rc = launch_merge_fused(s, X, idx, Z, Xm, wsb + w.fcache, w, st);
   } else {
-    if (!reuse_a) {  // (a cached A comes with its map)
-      rc = launch_weights(s, X, idx, A, Z, occ, wsb, w, st);
-      if (rc != TOMA_OK) return rc;
-    }
-    rc = launch_merge(s, X, A, Z, !reuse_a, occ, Xm, wsb, w, st);
+    rc = reuse_a ? launch_merge(s, X, A, Z, false, occ, Xm, wsb, w, st)  // (a cached A comes with its map)
+                 : weights_and_merge(s, X, idx, A, Z, occ, Xm, wsb, w, st);
   }
   if (rc != TOMA_OK) return rc;
   // inside the layer the attention writes its merged rows already divided by Z (the unmerge's

@@ -183,6 +183,9 @@ int launch_occupancy(const Shape &s, const void *A, uint8_t *occ, const Workspac
 // otherwise Z is read
 int launch_merge(const Shape &s, const void *X, const void *A, float *Z, bool make_z, const uint8_t *occ, void *Xm,
                  char *ws, const Workspace &w, hipStream_t st);
+// Fresh weights and the merge of small merge regions in one kernel (toma_local.hip): A, Z and Xm
+bool local_merge_fits(const Shape &s);
+int launch_local_merge(const Shape &s, const void *X, const int32_t *idx, void *A, float *Z, void *Xm, hipStream_t st);
 // Zs (optional): divide the merged rows of O by max(Z, 1e-20) on the way out (the unmerge input)
 // O_extra (optional): the extra-token rows go to O_extra [B, T, C] instead of rows D.. of O
 int launch_attend(const Shape &s, const void *Xm, const void *Xe, const void *Wq, const void *Wk,
@@ -215,7 +218,7 @@ int launch_mlp(int dtype, int rows, int C, int hidden, const void *In, const voi
 
 // Kernel identifiers of the profiling aid (toma_profile_*): one per kernel of the path.
 enum KernelId { K_LIMBS = 0, K_GRAM, K_GREEDY, K_WSTATS, K_LSE, K_WWRITE, K_ZSUM, K_MERGE, K_QKV, K_ATTN, K_PROJ,
-                K_SCALE, K_UNMERGE, K_SPLIT, K_MLP_UP, K_MLP_DOWN, K_OCC, K_PINV_EIG, K_PINV_APPLY, K_MERGE_FUSED, K_UNMERGE_FUSED, K_WBOUNDS, K_COUNT };
+                K_SCALE, K_UNMERGE, K_SPLIT, K_MLP_UP, K_MLP_DOWN, K_OCC, K_PINV_EIG, K_PINV_APPLY, K_MERGE_FUSED, K_UNMERGE_FUSED, K_WBOUNDS, K_LOCAL_MERGE, K_COUNT };
 
 // Brackets one launch with HIP events on its stream while profiling is enabled; free otherwise.
 struct KernelTimer {
