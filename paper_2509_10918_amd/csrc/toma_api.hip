@@ -47,6 +47,12 @@ int make_shape(const toma_desc *d, const toma_attn_desc *a, Shape *s) {
   return TOMA_OK;
 }
 
+// Room for the int8 similarities of regions of more than 256 tokens: behind the selection's state, in `bytes` of scratch.
+static void plan_big_gram(const Shape &s, size_t bytes, Workspace *w) {
+  const size_t at = up256(w->big + big_state_bytes(s)), need = gram_i8_big_bytes(s);
+  w->big_gram = need != 0 && at + need <= bytes ? at : 0;
+}
+
 void plan_workspace(const Shape &s, Workspace *w) {
   size_t es = s.dtype == TOMA_BF16 ? 2 : 4;
   size_t off = 0;
@@ -103,6 +109,7 @@ void plan_workspace(const Shape &s, Workspace *w) {
   w->total = off;
   w->big = w->stats;  // (the first section that the selection does not use)
   w->big_state = w->big + big_state_bytes(s) <= w->total;  // (always: stats and its like in fcache take 32 bytes per token)
+  w->big_gram = 0;  // (planned where the scratch at hand is known)
 }
 
 // Fresh weights and the merge with them: one kernel where a merge region is small enough.
@@ -124,6 +131,7 @@ static int prepare(const toma_desc *d, const toma_attn_desc *a, void *ws, size_t
   if (!ws) return TOMA_ERR_NULL;
   if (misaligned(ws, 256)) return TOMA_ERR_ALIGN;
   if (ws_bytes < w->total) return TOMA_ERR_WORKSPACE;
+  plan_big_gram(*s, ws_bytes, w);  // (a select without attention in its descriptors may still have a layer's scratch)
   return TOMA_OK;
 }
 
@@ -236,6 +244,7 @@ TOMA_API int toma_select_static(const toma_desc *desc, const void *X, int32_t *i
   rc = static_scratch(&buf);
   if (rc != TOMA_OK) return rc;
   w.big_state = w.big + big_state_bytes(s) <= (size_t)TOMA_STATIC_SCRATCH_BYTES;
+  plan_big_gram(s, (size_t)TOMA_STATIC_SCRATCH_BYTES, &w);
   return launch_select(s, X, idx, gain_opt, gap_opt, buf, w, static_cast<hipStream_t>(stream));
 }
 

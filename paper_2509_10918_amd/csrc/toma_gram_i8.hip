@@ -405,7 +405,7 @@ __global__ __launch_bounds__(256, NBUF == 3 ? 2 : 3) void k_gram_i8(const uint32
   }
 }
 
-size_t gram_i8_workspace_bytes(const Shape &s) {
+static size_t gram_i8_bytes(const Shape &s) {
   // (channels: the limb pass keeps a token's row in registers, up to 3072 of them; work: with the limb
   // pass in front and some 10 us of fixed cost per launch (first loads, norms, double-precision
   // combination, stores) the kernel only beats the fp64 one once there is enough to do - measured in
@@ -413,16 +413,18 @@ size_t gram_i8_workspace_bytes(const Shape &s) {
   // a quarter; 640 lose)
   const int nb64 = (s.n_loc + 63) / 64;
   const long long block_chunks = (long long)s.B * s.P * (nb64 * (nb64 + 1) / 2) * ((s.C + 63) / 64);
-  // (regions of more than 256 tokens take the selection kernel that has no fallback for flagged tokens)
-  if (s.dtype != TOMA_BF16 || s.C > 3072 || block_chunks < 3000 || s.n_loc > 256) return 0;
+  if (s.dtype != TOMA_BF16 || s.C > 3072 || block_chunks < 3000) return 0;
   const size_t rows = (size_t)s.B * s.N;
   const size_t words = (size_t)((s.C + 63) / 64) * 64;  // one word (four limbs) per channel of the padded row
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return up(rows * words * 4) + 2 * up(rows * sizeof(double)) + up(rows) + up(rows * sizeof(LimbFix));
 }
 
-// S for every region of a bf16 input; ws_part: gram_i8_workspace_bytes() bytes.  Leaves the per-token
-// norms and flags where the selection kernel's prologue finds them (returned through the pointers).
+size_t gram_i8_workspace_bytes(const Shape &s) { return s.n_loc <= 256 ? gram_i8_bytes(s) : 0; }
+size_t gram_i8_big_bytes(const Shape &s) { return s.n_loc > 256 ? gram_i8_bytes(s) : 0; }
+
+// S for every region of a bf16 input; ws_part: gram_i8_workspace_bytes() or gram_i8_big_bytes() bytes.  Leaves the per-token
+// norms and flags where the selection kernel's prologue (larger regions: k_big_fix) finds them (returned through the pointers).
 int launch_gram_i8(const Shape &s, const void *X, int32_t *S, char *ws_part, const double **nrm_out,
                    const uint8_t **flag_out, hipStream_t st) {
   const size_t rows = (size_t)s.B * s.N;

@@ -26,6 +26,8 @@ struct Workspace {
   // later stages use.  big_state: the scratch at hand has room for it (the kernels do without where it has not)
   size_t big;
   bool big_state;
+  // where the int8 similarities of those regions have their scratch, behind big; 0: no room (the fp64 kernel runs)
+  size_t big_gram;
   int stat_parts, z_parts;
   // occupancy map of A, kept by the caller next to (A, Z): blocks of kOccDest destinations x kOccSrc
   // sources per merge region (0: this shape uses none)
@@ -152,7 +154,8 @@ void plan_workspace(const Shape &s, Workspace *w);
 // Similarities of bf16 tokens on the int8 matrix cores (toma_gram_i8.hip): scratch size (0: this shape
 // takes the fp64 kernel instead) and launch; nrm_out / flag_out: per-token norms and the flags of tokens
 // whose rows of S the selection kernel has to recompute in double precision
-size_t gram_i8_workspace_bytes(const Shape &s);
+size_t gram_i8_workspace_bytes(const Shape &s);  // (a section of its own: regions of up to 256 tokens)
+size_t gram_i8_big_bytes(const Shape &s);        // (larger regions: scratch in later stages' room)
 int launch_gram_i8(const Shape &s, const void *X, int32_t *S, char *ws_part, const double **nrm_out,
                    const uint8_t **flag_out, hipStream_t st);
 // gain, gap: optional outputs (null: not wanted); parts: null, or where the profiling variant of the

@@ -1,7 +1,8 @@
 // Destination selection: cosine similarity inside each region and the greedy facility-location
 // pick sequence (paper Sec. 4.1, Eq. 2, Alg. 2; regions as in Alg. 3 step 1).
 //
-// Kernels (bf16 tokens in regions of up to 256 take their similarities from the int8 matrix cores, toma_gram_i8.hip):
+// Kernels (bf16 tokens with enough to do take their similarities from the int8 matrix cores, toma_gram_i8.hip; regions of
+// more than 256 tokens where the scratch behind the selection's own has room for it):
 //   k_gram    S = cos(x_i, x_j) per region with the fp64 matrix cores (v_mfma_f64_16x16x4_f64):
 //             products of stored bf16 / fp32 values are exact in double, so S is the similarity
 //             to ~1e-16 before it is rounded once to the nearest multiple of 2^-30 and stored as
@@ -226,6 +227,24 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t k) {
 // What the selection kernel needs to recompute flagged rows of S in double precision (flag == null: none).
 struct RowFix { const bf16_t *X; const double *nrm; const uint8_t *flag; int N, C; };
 
+// Product of two rows in double precision (exact products of bf16 values), a wave's lanes across the channels, eight each
+// per step.
+__device__ __forceinline__ double exact_dot(const bf16_t *xt, const bf16_t *xj, int C, int lane) {
+  double dot = 0.0;
+  for (int ch = 8 * lane; ch < C; ch += 512) {
+    const Pkt pa = pkt_load(xt + ch), pb = pkt_load(xj + ch);
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const uint32_t wa = pa.v[u], wb = pb.v[u];
+      dot += (double)__builtin_bit_cast(float, wa << 16) * (double)__builtin_bit_cast(float, wb << 16);
+      dot += (double)__builtin_bit_cast(float, wa & 0xffff0000u) * (double)__builtin_bit_cast(float, wb & 0xffff0000u);
+    }
+  }
+#pragma unroll
+  for (int msk = 1; msk < 64; msk <<= 1) dot += wave_xor_f64(dot, msk);
+  return dot;
+}
+
 constexpr uint64_t kNoRunnerUp = ~0ull;  // recorded gap when the pick was the last candidate
 
 // CLOCKS (a profiling aid, never the product's kernel): every wave also adds up the shader clocks it
@@ -271,22 +290,10 @@ __global__ __launch_bounds__(64 * ((NT + 1) / 2)) void k_greedy(int32_t *S, int3
         if (!((fbits[t >> 5] >> (t & 31)) & 1u)) continue;  // (uniform)
         const size_t tt = tok0 + map.token(p, t);
         const bf16_t *xt = fix.X + tt * fix.C;
-        // a wave per partner token, its lanes across the channels (eight each per step)
+        // a wave per partner token
         for (int j = w; j < NL; j += NW) {
           const size_t tj = tok0 + map.token(p, j);
-          const bf16_t *xj = fix.X + tj * fix.C;
-          double dot = 0.0;
-          for (int ch = 8 * lane; ch < fix.C; ch += 512) {
-            const Pkt pa = pkt_load(xt + ch), pb = pkt_load(xj + ch);
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-              const uint32_t wa = pa.v[u], wb = pb.v[u];
-              dot += (double)__builtin_bit_cast(float, wa << 16) * (double)__builtin_bit_cast(float, wb << 16);
-              dot += (double)__builtin_bit_cast(float, wa & 0xffff0000u) * (double)__builtin_bit_cast(float, wb & 0xffff0000u);
-            }
-          }
-#pragma unroll
-          for (int msk = 1; msk < 64; msk <<= 1) dot += wave_xor_f64(dot, msk);
+          const double dot = exact_dot(xt, fix.X + tj * fix.C, fix.C, lane);
           if (lane == 0) {
             const int32_t v = (int32_t)rint(dot / (fix.nrm[tt] * fix.nrm[tj]) * kSimScale);
             Sr[(size_t)t * NL + j] = v;
@@ -588,6 +595,27 @@ constexpr int kCandHeld = 8;    // candidates that may exceed one column's cover
 // changed columns per pick up to which rounds take several picks, and up to which they take them from the longer list
 constexpr int kSparse = 64, kSparser = 12;
 constexpr int kBackMax = 15;    // rounds of one pick between two searches for several that fail, at most
+
+// The flagged rows (see k_greedy) of regions of more than 256 tokens, before anything reads S: a wave per token, which
+// nearly always finds no flag (launch latency: 4 us).  With it the int8 similarities serve these regions too: four of
+// 1024 tokens, two samples, 640 channels, the layer 1226 us with the fp64 kernel's 137 us of similarities and 1145 without.
+__global__ __launch_bounds__(256) void k_big_fix(int32_t *__restrict__ S, RegionMap map, int P, int n, int tokens, RowFix fix) {
+  const int z = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (z >= tokens) return;
+  const int bp = z / n, t = z - bp * n, p = bp % P;
+  const size_t tok0 = (size_t)(bp / P) * fix.N, tt = tok0 + map.token(p, t);
+  if (fix.flag[tt] != 2) return;
+  int32_t *Sr = S + (size_t)bp * n * n;
+  for (int j = 0; j < n; j++) {
+    const size_t tj = tok0 + map.token(p, j);
+    const double dot = exact_dot(fix.X + tt * fix.C, fix.X + tj * fix.C, fix.C, lane);
+    if (lane == 0) {  // (two flagged tokens write the same value twice)
+      const int32_t v = (int32_t)rint(dot / (fix.nrm[tt] * fix.nrm[tj]) * kSimScale);
+      Sr[(size_t)t * n + j] = v;
+      Sr[(size_t)j * n + t] = v;
+    }
+  }
+}
 
 // State of the selection of one large region between kernels: keys (0 = picked), coverage, picks so far.
 struct BigState { uint64_t *key; int32_t *m; uint64_t *pick; };
@@ -980,11 +1008,12 @@ static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, f
   RegionMap map{s.W, s.tile_h, s.tile_w, s.W / s.tile_w};
   const int tiles = s.n_loc / 16, units = tiles * (tiles + 1) / 2;
   RowFix fix{nullptr, nullptr, nullptr, s.N, s.C};
-  if (sizeof(T) == 2 && gram_i8_workspace_bytes(s) != 0) {
+  const size_t gram_at = s.n_loc > 256 ? w.big_gram : gram_i8_workspace_bytes(s) != 0 ? w.gram : 0;
+  if (sizeof(T) == 2 && gram_at != 0) {
     // bf16 tokens: exact similarities on the int8 matrix cores
     const double *nrm = nullptr;
     const uint8_t *flag = nullptr;
-    const int rc = launch_gram_i8(s, X, S, ws + w.gram, &nrm, &flag, st);
+    const int rc = launch_gram_i8(s, X, S, ws + gram_at, &nrm, &flag, st);
     if (rc != TOMA_OK) return rc;
     fix = RowFix{reinterpret_cast<const bf16_t *>(X), nrm, flag, s.N, s.C};
   } else
@@ -1009,6 +1038,10 @@ static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, f
   }
   KernelTimer kt(K_GREEDY, st);
   if (s.n_loc > 256) {  // (regions too large for the register-resident kernel)
+    if (fix.flag) {
+      const int tokens = s.B * s.N;  // (every token is in one region)
+      hipLaunchKernelGGL(k_big_fix, dim3((tokens + 3) / 4), dim3(256), 0, st, S, map, s.P, s.n_loc, tokens, fix);
+    }
     const int threads = std::min(kBigThreads, (s.n_loc + 63) / 64 * 64);
     // The first n / kBigFirst picks one launch each (the variant that records gaps: none; without room for the
     // state - the library's static buffer may be full - the kernel starts from nothing).

@@ -359,6 +359,48 @@ def test_select_with_elements_far_below_a_tokens_largest(oracle, C, heads):
     assert np.allclose(dv.gain.cpu().numpy(), gain_ref, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("grid,tile,C,keep,layer_ws", [
+    ((32, 32), (32, 32), 768, 0.5, True),     # only the layer's scratch has room for the int8 similarities
+    ((64, 64), (32, 32), 640, 0.5, False),
+    ((72, 48), (24, 24), 672, 0.5, False),     # 576 tokens, half a channel chunk of padding
+    ((68, 48), (17, 48), 640, 0.5, False),     # 816 tokens: no multiple of a row block
+])
+def test_select_large_regions_in_fixed_point(oracle, grid, tile, C, keep, layer_ws):
+    """bf16 tokens of regions of more than 256 tokens, compared in fixed point with tokens whose rows are recomputed
+    among them: the oracle's picks, with scratch that has room for it and with too little (the double-precision kernel)."""
+    H, Wd = grid
+    w = synth.scaled(W["sdxl1"], name="bigrange", B=2, H=H, W=Wd, C=C, tile_h=tile[0], tile_w=tile[1], keep=keep,
+                     heads=C // 32, sigma=1.5, index=61)
+    nb = (w.n_loc + 63) // 64
+    assert w.B * w.P * (nb * (nb + 1) // 2) * ((C + 63) // 64) >= 3000
+    print(f"[select large regions, fixed point] grid {H}x{Wd} tile {tile} d_loc={w.d_loc} C={C}", flush=True)
+    inp = synth.make_inputs(w)
+    _, _, token_of = oracle.region_map(w.H, w.W, w.tile_h, w.tile_w)
+    X = inp["X"].copy()
+    X[0, token_of[0][5], 17] = 3e-9              # added back
+    X[1, token_of[-1][w.n_loc - 1], C - 32] = 2.5e6   # everything else of the token far below: rows recomputed
+    X[1, token_of[-1][3], 3] = -1.0e6            # (two of a region)
+    X[0, token_of[0][200]] = 0.0
+    inp["X"] = synth.round_to_bf16(X)
+    dv = tg.Device(w, inp, 1)
+    desc = dv.desc
+    need = tb.toma_workspace_bytes(desc, None)
+    idx_ref, gain_ref, _ = oracle.select(tg.oracle_desc(oracle, w, 1), _f64(inp["X"]))
+    for ws in (dv.ws, dv.ws[:need]) if layer_ws else (dv.ws[:need],):
+        dv.idx.zero_()
+        tb.toma_profile_enable(True)
+        try:
+            tb.toma_profile_read("limbs")
+            tb.toma_select(desc, dv.X, dv.idx, dv.gain, None, ws)
+            fixed_point, _ = tb.toma_profile_read("limbs")
+        finally:
+            tb.toma_profile_enable(False)
+        print(f"  scratch {ws.numel()}: fixed point {fixed_point}", flush=True)
+        assert fixed_point == (1 if ws is dv.ws or not layer_ws else 0)
+        assert np.array_equal(dv.idx.cpu().numpy().reshape(idx_ref.shape), idx_ref)
+        assert np.allclose(dv.gain.cpu().numpy().reshape(gain_ref.shape), gain_ref, rtol=1e-6, atol=1e-6)
+
+
 def _check_stage(name, got, ref, tol):
     err = tg.max_rel(got, ref)
     ex = tg.elem_excess(got, ref, tol)
