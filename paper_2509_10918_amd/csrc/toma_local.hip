@@ -13,7 +13,10 @@
 // eight tiles per wave); a deeper ring changed nothing (six stages: 14.2 us where three took 13.6), branches inside the
 // step cost a fifth of it.  Measured (us, the separate kernels and this one): regions of 64 tokens with 32 destinations,
 // width 1280, 128 regions 43.5 and 16.9; 64 with 16, 32 regions 28.8 and 13.0; 96 with 29, width 352, 45 regions 30 and 10;
-// 16 with 8, width 320, 2048 regions 96 and 26; fp32 64 with 32, width 640, 48 regions 46 and 20.
+// 16 with 8, width 320, 2048 regions 96 and 26.
+// bf16 only.  fp32 gained as well (64 with 32, width 640, 48 regions 46 and 20 us), but its exact softmax differs from the
+// one by a rounded log-sum-exp, which everything else of this path stores, by up to 1e-4 of a weight: weights kept from
+// one call for the next would no longer be the same whichever size they came from.
 #include <type_traits>
 
 #include "toma_gemm.h"
@@ -26,7 +29,8 @@ constexpr int kLocalLds = 156 * 1024, kLocalLds2 = 78 * 1024;  // (one workgroup
 
 // LDS of a region: the ring (whose room the logits and weights take over) and the slice's steps of the source rows
 struct LocalPlan { int nti, ntj, steps, stages, slices, per_slice; size_t ring, lds; };
-static bool plan_local(int regions, int Nr, int Dr, int C, int es, LocalPlan *best) {
+static bool plan_local(int regions, int Nr, int Dr, int C, LocalPlan *best) {
+  constexpr int es = 2;
   LocalPlan p;
   p.nti = Nr / 16;
   p.ntj = (Dr + 15) / 16;
@@ -53,11 +57,12 @@ static bool plan_local(int regions, int Nr, int Dr, int C, int es, LocalPlan *be
 }
 
 // NL: load instructions per wave and step (64 rows each); TPW: logit tiles per wave; ST: stages of the ring
-template <typename T, int NL, int TPW, int ST, int LDSB>
-__global__ __launch_bounds__(512) void k_local_merge(const RegionView<T> v, const int32_t *__restrict__ idx, float scale,
-                                                     T *__restrict__ A, float *__restrict__ Z, T *__restrict__ Xm, int ntj,
+template <int NL, int TPW, int ST, int LDSB>
+__global__ __launch_bounds__(512) void k_local_merge(const RegionView<bf16_t> v, const int32_t *__restrict__ idx, float scale,
+                                                     bf16_t *__restrict__ A, float *__restrict__ Z, bf16_t *__restrict__ Xm, int ntj,
                                                      int slices, int per_slice, int ring_bytes) {
-  constexpr int ES = (int)sizeof(T), EPS = 128 / ES, EPP = 16 / ES, NH = ES == 2 ? 2 : 1;
+  typedef bf16_t T;
+  constexpr int ES = (int)sizeof(T), EPS = 128 / ES, EPP = 16 / ES, NH = 2;
   constexpr int CPS = EPS / 16;  // 16-channel tiles per step
   __shared__ __align__(1024) char lds[LDSB];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
@@ -66,7 +71,7 @@ __global__ __launch_bounds__(512) void k_local_merge(const RegionView<T> v, cons
   const int z = work / slices, slice = work - z * slices, b = z / v.R, rho = z % v.R;
   const int Nr = v.Nr, Dr = v.Dr, C = v.C, Drp = 16 * ntj, rows = Nr + Drp, Nrp = (Nr + 31) / 32 * 32;
   const int steps = (C * ES + 127) / 128, k0 = slice * per_slice, k1 = min(k0 + per_slice, steps);
-  const int tail = C * ES - (steps - 1) * 128;  // bytes of the last step: 128, or 64 (bf16, C an odd multiple of 32)
+  const int tail = C * ES - (steps - 1) * 128;  // bytes of the last step: 128, or 64 (C an odd multiple of 32)
   const T *Xb = v.X + (size_t)b * v.N * C;
   char *kept = lds + ring_bytes;
 
@@ -216,18 +221,13 @@ __global__ __launch_bounds__(512) void k_local_merge(const RegionView<T> v, cons
       Frag<T> fa, fb;
       frag_load_kc(fa, P + (16 * tj + c) * ldp + 32 * kk + 8 * g);
       const int ra = 32 * kk + 8 * g;
-      if constexpr (ES == 2) {
-        typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
-        const int r = ra + (c >> 2), col = nb + 4 * (c & 3);
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(x + SwzTile<T>::kc(r, col >> 3) + (col & 7)));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(x + SwzTile<T>::kc(r + 4, col >> 3) + (col & 7)));
-        const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        fb.v = __builtin_bit_cast(bf16x8, both);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; e++) fb.v[e] = x[SwzTile<T>::kc(ra + e, (nb + c) >> 2) + ((nb + c) & 3)];
-      }
+      typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      const int r = ra + (c >> 2), col = nb + 4 * (c & 3);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(x + SwzTile<T>::kc(r, col >> 3) + (col & 7)));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(x + SwzTile<T>::kc(r + 4, col >> 3) + (col & 7)));
+      const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      fb.v = __builtin_bit_cast(bf16x8, both);
       mma16(o, fb, fa);    // lane: destination c, channels 4 g + r
       mma16(rs, ones, fa);  // the destination's row sum
     }
@@ -240,38 +240,32 @@ __global__ __launch_bounds__(512) void k_local_merge(const RegionView<T> v, cons
 }
 
 // Where it pays.  In us, fitted to traces of both over regions of 16 to 192 tokens with 1 to 8 tiles per wave, widths of
-// 64 to 1280 and grids of up to 1280 workgroups: per round of one or two workgroups per CU, a fixed part, the softmax, the K
-// steps and (fp32) the merge of the slice; against the fixed cost of four or five kernels, their K steps, the passes over X
-// and a block tile at least per region.
-// Both sides at the line: bf16 144 tokens with 72 destinations, width 1280, 32 regions 35.7 and 40.1, 128 regions (four
-// rounds) 118 and 74; 128 with 112, width 1280, 35.3 and 31.6.  Destinations in one block of 128 have a one-pass kernel
-// (128 tokens with 128: 11 us against 15).
+// 64 to 1280 and grids of up to 1280 workgroups: per round of one or two workgroups per CU, a fixed part, the softmax and
+// the K steps; against the fixed cost of four or five kernels, their K steps, the passes over X and a block tile at least
+// per region.  Both sides at the line: 144 tokens with 72 destinations, width 1280, 32 regions 35.7 and 40.1, 128 regions
+// (four rounds) 118 and 74; 128 with 112, width 1280, 35.3 and 31.6.  Destinations in one block of 128 have a one-pass
+// kernel (128 tokens with 128: 11 us against 15).
 bool local_merge_fits(const Shape &s) {
-  const bool f32 = s.dtype != TOMA_BF16;
-  const int es = f32 ? 4 : 2, regions = s.B * s.R;
+  const int regions = s.B * s.R;
   LocalPlan p;
-  if (!plan_local(regions, s.Nr, s.Dr, s.C, es, &p)) return false;
-  if (weights_single_pass(s.Nr, s.Dr, s.C, regions, es)) return false;
-  const int per_wave = (p.nti * p.ntj + 7) / 8;
-  const int at_once = p.lds <= (size_t)kLocalLds2 ? 512 : 256;
-  const double rounds = (double)(((long long)regions * p.slices + at_once - 1) / at_once), mb = (double)s.B * s.N * s.C * es * 1e-6;
-  const double step = f32 ? 0.5 + 0.3 * per_wave : 0.25 + 0.1 * per_wave;
-  const double here = rounds * (5.0 + 1.2 * per_wave + p.steps * step + (f32 ? 0.8 * p.per_slice : 0.0));
-  const double separate = 17.0 + (f32 ? 1.1 : 0.55) * p.steps + (f32 ? 0.85 : 0.6) * mb + 0.03 * regions;
-  return here < 0.95 * separate;
+  if (s.dtype != TOMA_BF16 || !plan_local(regions, s.Nr, s.Dr, s.C, &p)) return false;
+  if (weights_single_pass(s.Nr, s.Dr, s.C, regions, 2)) return false;
+  const int per_wave = (p.nti * p.ntj + 7) / 8, at_once = p.lds <= (size_t)kLocalLds2 ? 512 : 256;
+  const double rounds = (double)(((long long)regions * p.slices + at_once - 1) / at_once), mb = (double)s.B * s.N * s.C * 2e-6;
+  const double here = rounds * (5.0 + 1.2 * per_wave + p.steps * (0.25 + 0.1 * per_wave));
+  return here < 0.95 * (17.0 + 0.55 * p.steps + 0.6 * mb + 0.03 * regions);
 }
 
-template <typename T>
-static int local_typed(const Shape &s, const void *X, const int32_t *idx, void *A, float *Z, void *Xm, hipStream_t st) {
+int launch_local_merge(const Shape &s, const void *X, const int32_t *idx, void *A, float *Z, void *Xm, hipStream_t st) {
   LocalPlan p;
-  if (!plan_local(s.B * s.R, s.Nr, s.Dr, s.C, (int)sizeof(T), &p)) return TOMA_ERR_UNSUPPORTED;
-  const RegionView<T> v = make_view<T>(s, X);
+  if (s.dtype != TOMA_BF16 || !plan_local(s.B * s.R, s.Nr, s.Dr, s.C, &p)) return TOMA_ERR_UNSUPPORTED;
+  const RegionView<bf16_t> v = make_view<bf16_t>(s, X);
   const int rows = s.Nr + 16 * p.ntj, per_wave = (p.nti * p.ntj + 7) / 8;
   const dim3 grid((unsigned)(s.B * s.R * p.slices));
   KernelTimer kt(K_LOCAL_MERGE, st);
-#define TOMA_LOCAL_LDS(NL, TPW, ST, LDSB)                                                                            \
-  hipLaunchKernelGGL((k_local_merge<T, NL, TPW, ST, LDSB>), grid, dim3(512), 0, st, v, idx, s.scale,                  \
-                     static_cast<T *>(A), Z, static_cast<T *>(Xm), p.ntj, p.slices, p.per_slice, (int)p.ring)
+#define TOMA_LOCAL_LDS(NL, TPW, ST, LDSB)                                                                           \
+  hipLaunchKernelGGL((k_local_merge<NL, TPW, ST, LDSB>), grid, dim3(512), 0, st, v, idx, s.scale,                    \
+                     static_cast<bf16_t *>(A), Z, static_cast<bf16_t *>(Xm), p.ntj, p.slices, p.per_slice, (int)p.ring)
 #define TOMA_LOCAL(NL, TPW, ST)                                                                                     \
   do {                                                                                                              \
     if (p.lds <= (size_t)kLocalLds2) TOMA_LOCAL_LDS(NL, TPW, ST, kLocalLds2);                                       \
@@ -286,10 +280,6 @@ static int local_typed(const Shape &s, const void *X, const int32_t *idx, void *
 #undef TOMA_LOCAL_LDS
 #undef TOMA_LOCAL
   return launch_status();
-}
-
-int launch_local_merge(const Shape &s, const void *X, const int32_t *idx, void *A, float *Z, void *Xm, hipStream_t st) {
-  return s.dtype == TOMA_BF16 ? local_typed<bf16_t>(s, X, idx, A, Z, Xm, st) : local_typed<float>(s, X, idx, A, Z, Xm, st);
 }
 
 }  // namespace toma
