@@ -134,9 +134,9 @@ inline bool weights_single_pass(int Nr, int Dr, int C, int batch, int elem_size)
 // Does screening the weights (toma_screen.hip) pay?  In shader clocks: its three launches about 60000, 1500 per K step
 // (the exact products are bound by latency), and writing A and comparing 0.0022 per weight; the full product as priced
 // above.  Measured (us, full and screened): 128 x 128 grid 645 and 250; SDXL's first stage 45 and 44, a Flux block 59 and
-// 79 (long rows), fp32 rows of 1280 on a 32 x 32 grid 61 and 107.
+// 79 (long rows).
 inline bool screen_pays(const Shape &s) {
-  const int es = s.dtype == TOMA_BF16 ? 2 : 4;
+  const int es = 2;
   if (!gemm_async_fits(s.Nr, s.Dr, s.C, es)) return false;
   const int batch = s.B * s.R;
   double full;

@@ -791,19 +791,21 @@ static int weights_typed(const Shape &s, const void *X, const int32_t *idx, void
   const int zr = s.B * s.D;
   // partial row sums of the stored weights, for k_zsum: not needed where the merge product makes Z
   float *zpart = w.z_in_merge ? nullptr : reinterpret_cast<float *>(ws + w.zpart);
-  const ScreenPlan screen = plan_screen(s, w);
-  if (screen.use) {
-    const int rc = launch_screen(s, screen, X, idx, A, ws, st);
-    if (rc != TOMA_OK) return rc;
-    const int tiles = (s.N + 31) / 32;
-    KernelTimer kt(K_WWRITE, st);
-    const RegionView<T> v = make_view<T>(s, X);
-    const int2 *order = reinterpret_cast<const int2 *>(ws + screen.order);
-    const uint8_t *act = reinterpret_cast<const uint8_t *>(ws + screen.act);
-    uint8_t *occ = w.occ_sb ? occ_out : nullptr;
-    hipLaunchKernelGGL((k_weights_sparse<T>), dim3(tiles * s.B), dim3(512), 0, st, v, order, s.scale, static_cast<T *>(A), act,
-                       screen.act_row, occ, w.occ_db, w.occ_sb, tiles);
-    return launch_status();
+  if constexpr (sizeof(T) == 2) {
+    const ScreenPlan screen = plan_screen(s, w);
+    if (screen.use) {
+      const int rc = launch_screen(s, screen, X, idx, A, ws, st);
+      if (rc != TOMA_OK) return rc;
+      const int tiles = (s.N + 31) / 32;
+      KernelTimer kt(K_WWRITE, st);
+      const RegionView<T> v = make_view<T>(s, X);
+      const int2 *order = reinterpret_cast<const int2 *>(ws + screen.order);
+      const uint8_t *act = reinterpret_cast<const uint8_t *>(ws + screen.act);
+      uint8_t *occ = w.occ_sb ? occ_out : nullptr;
+      hipLaunchKernelGGL((k_weights_sparse<T>), dim3(tiles * s.B), dim3(512), 0, st, v, order, s.scale, static_cast<T *>(A), act,
+                         screen.act_row, occ, w.occ_db, w.occ_sb, tiles);
+      return launch_status();
+    }
   }
   if (weights_single_pass(s.Nr, s.Dr, s.C, batch, (int)sizeof(T))) {
     const RegionView<T> v = make_view<T>(s, X);

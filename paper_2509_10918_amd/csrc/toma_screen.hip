@@ -1,8 +1,7 @@
 // Which merge weights can be nonzero at all: a bound on every logit of the global merge from a 4-bit product.
 //
 // The merge weights are a softmax over all destinations of a sample, at a small temperature: a source's largest logit
-// stands hundreds of units above nearly all others, whose weights are then below e^-110 and exact zeros in bf16 and
-// fp32 alike.  Which tiles of 32 sources x 16 destinations hold anything else is found without the full product:
+// stands hundreds of units above nearly all others, whose weights are then below e^-110 and exact zeros.  Which tiles of 32 sources x 16 destinations hold anything else is found without the full product:
 //   k_fp4_bounds  per token: the row rounded to 4-bit floats (e2m1, one scale per token) with the exact norm of what
 //                 the rounding dropped; per source a lower bound on its largest logit, the exact product with the
 //                 destinations of its own selection region.
@@ -42,11 +41,6 @@ __device__ __forceinline__ void load8(float (&x)[8], const bf16_t *p) {
     x[2 * i] = __builtin_bit_cast(float, u << 16);
     x[2 * i + 1] = __builtin_bit_cast(float, u & 0xffff0000u);
   }
-}
-__device__ __forceinline__ void load8(float (&x)[8], const float *p) {
-  const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
-#pragma unroll
-  for (int i = 0; i < 4; i++) { x[i] = a[i]; x[4 + i] = b[i]; }
 }
 // operand of a product of 4-bit floats: 32 of them in the first four registers
 __device__ __forceinline__ i32x8 four_bit(const u32x4 &q) { return (i32x8){(int)q[0], (int)q[1], (int)q[2], (int)q[3], 0, 0, 0, 0}; }
@@ -328,10 +322,11 @@ __global__ __launch_bounds__(512) void k_screen(const RegionView<T> v, const int
 
 ScreenPlan plan_screen(const Shape &s, const Workspace &w) {
   ScreenPlan p{};
-  const int es = s.dtype == TOMA_BF16 ? 2 : 4;
+  // bf16 only: the exact kernel's fp32 weights differ from the full product's in the last place of a log-sum-exp of some
+  // thousands, up to 1e-4 of a weight, and weights kept for later calls have to be the same whichever kernel made them.
   // (a merge region of one selection region has no far destinations; rows of a multiple of 128 bytes and at most 3072
   // channels are what the kernels take, and a list of marked tiles has room for 32768 destinations)
-  if (s.R != 1 || s.P < 4 || (s.C * es) % 128 != 0 || s.C > 3072 || s.D > 32768 || !w.z_in_merge) return p;
+  if (s.dtype != TOMA_BF16 || s.R != 1 || s.P < 4 || s.C % 64 != 0 || s.C > 3072 || s.D > 32768 || !w.z_in_merge) return p;
   auto up256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
   p.kc = (s.C + 127) / 128;
   p.act_row = (s.D + 127) / 128;
@@ -385,7 +380,7 @@ static int screen_typed(const Shape &s, const ScreenPlan &p, const void *X, cons
 }
 
 int launch_screen(const Shape &s, const ScreenPlan &p, const void *X, const int32_t *idx, void *A, char *ws, hipStream_t st) {
-  return s.dtype == TOMA_BF16 ? screen_typed<bf16_t>(s, p, X, idx, A, ws, st) : screen_typed<float>(s, p, X, idx, A, ws, st);
+  return screen_typed<bf16_t>(s, p, X, idx, A, ws, st);
 }
 
 }  // namespace toma

@@ -536,12 +536,11 @@ def test_merge_unmerge_skip_only_empty_blocks(oracle, dtype, tau, C, passes):
 @pytest.mark.parametrize("dtype,grid,tile,d_loc,C,tau,how", [
     ("bf16", (64, 80), (16, 16), 192, 256, 0.1, ""),         # D = 3840: whole tiles of 16 destinations
     ("bf16", (72, 72), (12, 12), 71, 704, 0.1, ""),          # blocks of 32 sources in two regions, D = 2556: a ragged last tile
-    ("f32", (64, 80), (16, 16), 192, 320, 0.1, ""),
+    ("bf16", (64, 80), (16, 16), 192, 320, 0.1, ""),
     ("bf16", (64, 80), (16, 16), 192, 256, 100.0, ""),       # no tile is empty: more than 128 per block, in chunks, twice
-    ("f32", (64, 80), (16, 16), 192, 320, 3.0, ""),          # some are
+    ("bf16", (64, 80), (16, 16), 192, 320, 3.0, ""),         # some are
     ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "repeated"),  # destinations that repeat and lie outside their region
-    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "uneven"),    # zero, tiny and large tokens
-    ("f32", (32, 64), (8, 8), 48, 3072, 0.1, "")])           # the longest rows that are screened
+    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "uneven")])   # zero, tiny and large tokens
 def test_screened_merge_weights(oracle, dtype, grid, tile, d_loc, C, tau, how):
     """Weights of large global merges, whose tiles are screened by a 4-bit product first: A / Z, Z and merged tokens
     against the oracle, and the block map by way of the unmerge."""
