@@ -75,23 +75,40 @@ inline GemmPlan plan_gemm_async(int M, int N, int K, int batch, int elem_size, b
   static const int step[3][5] = {{3230, 2200, 1230, 1000, 560},   // both operands k-contiguous
                                  {3700, 1900, 1300, 810, 560},    // one k-major
                                  {3400, 2100, 1220, 750, 560}};   // both k-major
+  // fp32 with plain stores: bound by the matrix cores at any tile, so that the narrow tile, which fills the chip best, is
+  // nearly always the best one.  The figures of bf16 (used before) split K or took 128 wide tiles too often: us, before and
+  // 64 x 64: QKV of 1536 rows, width 960, 129 and 94, of 1152 rows, width 640, 52 and 43; unmerge of 2304 tokens with 1152
+  // destinations, width 640, 26.5 and 22, of 1024 with 512, width 1280, batch 2, 43.5 and 37.6.  The last round counts
+  // by what it holds, and a workgroup alone on its CU takes 1.25 times its share of two.
+  static const int step_f32[5] = {20500, 10250, 5200, 2900, 1450};
   static const int per_cu[5] = {1, 1, 1, 2, 2};
+  const bool f32 = elem_size == 4 && epi == 1;
   const int kind = (a_ks ? 1 : 0) + (b_ks ? 1 : 0);
   const int nk = K / (128 / elem_size);
   GemmPlan best{128, 128, 1, 0.0};
   double best_cost = -1.0;
-  for (int i = 0; i < 5; i++) {
-    const long long tiles = (long long)((M + bm[i] - 1) / bm[i]) * ((N + bn[i] - 1) / bn[i]) * batch;
-    for (int ns = 1; ns <= (may_split ? 8 : 1); ns++) {
-      if (ns > 1 && nk / ns < 8) break;
-      const long long blocks = tiles * ns, slots = 256ll * per_cu[i];
-      const long long rounds = (blocks + slots - 1) / slots;
-      const double fixed = 4000.0 + epi * bm[i] * bn[i] / 8.0;
-      const long long share = std::min<long long>(per_cu[i], (blocks + 255) / 256);  // workgroups sharing a CU
-      double cost = rounds * (((nk + ns - 1) / ns) * (double)step[kind][i] * share + fixed);
-      if (ns > 1) cost += 8000.0 + (4.0 * ns + elem_size) * (double)M * N * batch / 1500.0;
-      if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = GemmPlan{bm[i], bn[i], ns, cost}; }
+  int most = may_split ? 8 : 1;  // K split: (fp32) never more than the bf16 figures give, which the scratch was sized by
+  for (int pass = f32 && may_split ? 0 : 1; pass < 2; pass++) {
+    best_cost = -1.0;
+    for (int i = 0; i < 5; i++) {
+      const long long tiles = (long long)((M + bm[i] - 1) / bm[i]) * ((N + bn[i] - 1) / bn[i]) * batch;
+      for (int ns = 1; ns <= most; ns++) {
+        if (ns > 1 && nk / ns < 8) break;
+        const long long blocks = tiles * ns, slots = 256ll * per_cu[i];
+        const long long rounds = (blocks + slots - 1) / slots;
+        const double fixed = 4000.0 + epi * bm[i] * bn[i] / 8.0;
+        const long long share = std::min<long long>(per_cu[i], (blocks + 255) / 256);  // workgroups sharing a CU
+        double cost = rounds * (((nk + ns - 1) / ns) * (double)step[kind][i] * share + fixed);
+        if (f32 && pass == 1) {
+          const long long rest = blocks % slots;
+          const double one = (nk + ns - 1) / ns * (double)step_f32[i], last = rest > 256 || per_cu[i] == 1 ? per_cu[i] : 1.25;
+          cost = (double)(blocks / slots) * (one * per_cu[i] + fixed) + (rest ? one * last + fixed : 0.0);
+        }
+        if (ns > 1) cost += 8000.0 + (4.0 * ns + elem_size) * (double)M * N * batch / 1500.0;
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = GemmPlan{bm[i], bn[i], ns, cost}; }
+      }
     }
+    most = best.nsplit;
   }
   return best;
 }

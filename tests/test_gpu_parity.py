@@ -695,6 +695,30 @@ def test_merge_unmerge_of_few_k_steps(oracle, dtype, tile, d_loc):
     _check_stage("Y", dv.unmerge(O=O), oracle.unmerge(d, A, Z, _f64(O)), tol)
 
 
+@pytest.mark.parametrize("grid,tile,d_loc,C", [
+    ((48, 64), (8, 8), 16, 96),    # a K split of the narrow tile
+    ((40, 72), (8, 12), 29, 352),  # ragged rows and columns
+    ((64, 64), (16, 16), 40, 320),  # more workgroups than fit at once
+])
+def test_fp32_products_of_planned_tiles(oracle, grid, tile, d_loc, C):
+    """fp32 merge and unmerge of whole samples against dense weights: at most N roundings of 2^-24 per sum."""
+    w = synth.scaled(W["tiny"], name="f32plan", dtype="f32", B=2, H=grid[0], W=grid[1], C=C, tile_h=tile[0], tile_w=tile[1],
+                     keep=d_loc / (tile[0] * tile[1]), heads=C // 32, index=67)
+    assert w.d_loc == d_loc
+    print(f"[fp32 products] grid {grid} D={w.D} C={C}", flush=True)
+    inp = synth.make_inputs(w)
+    rng = np.random.default_rng(68)
+    d = tg.oracle_desc(oracle, w, 1)
+    dv = tg.Device(w, inp, 1)
+    A = _f64(rng.uniform(0.0, 1.0, (w.B, 1, w.D, w.N)).astype(np.float32))
+    Z = A.sum(axis=3).reshape(w.B, w.D)
+    dv.plant(A, Z)
+    tol = w.N * 2.0 ** -24
+    _check_stage("Xm", dv.merge_cached(), oracle.merge(d, _f64(inp["X"]), A, Z), tol)
+    O = synth.quantize(w, rng.standard_normal((w.B, w.D, w.C)).astype(np.float32))
+    _check_stage("Y", dv.unmerge(O=O), oracle.unmerge(d, A, Z, _f64(O)), tol)
+
+
 @pytest.mark.parametrize("tile_local", [False, True])
 @pytest.mark.parametrize("name", list(CASES))
 def test_layer_chained_and_reuse(oracle, cases, name, tile_local):
