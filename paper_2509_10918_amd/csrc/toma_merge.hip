@@ -395,6 +395,7 @@ __global__ __launch_bounds__(512) void k_weights_fused(const RegionView<T> v, co
 // workgroup of 32 sources with the marked tiles in place of all destinations, 1 to 16 per wave as the list asks.
 // Where more than 128 are marked (a softmax that is not sharp), they are walked in chunks of 128 twice: statistics, then
 // weights.
+// A source whose sum is not finite (a logit that is NaN or +infinity) has no zero weights, and its other ones are NaN too.
 constexpr int kListMax = 2048;   // destination tiles (32768 destinations)
 template <typename T>
 __global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, const int2 *__restrict__ order, float scale,
@@ -486,7 +487,7 @@ __global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, c
         const float before = m;
 #pragma unroll
         for (int q = 0; q < 8; q++) { m = fmaxf(m, red[0][q][tid]); sum += red[1][q][tid]; }  // (fixed order)
-        row_sum[tid] = (row_sum[tid] > 0.f ? row_sum[tid] * __builtin_amdgcn_exp2f((before - m) * k2) : 0.f) + sum;
+        row_sum[tid] = row_sum[tid] * __builtin_amdgcn_exp2f((before - m) * k2) + sum;  // (the first: 0 exp(-inf); NaN stays)
         row_max[tid] = m;
       }
       __syncthreads();
@@ -548,6 +549,12 @@ __global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, c
   else if (na > 16) run(std::integral_constant<int, 4>{});
   else if (na > 8) run(std::integral_constant<int, 2>{});
   else if (na > 0) run(std::integral_constant<int, 1>{});
+  if (__syncthreads_or(tid < 32 && !(row_sum[tid & 31] < __builtin_inff()))) {
+    for (int e = tid; e < v.Dr * 32; e += 512)
+      if (m0 + (e & 31) < v.Nr && !(row_sum[e & 31] < __builtin_inff()))
+        A[((size_t)b * v.Dr + (e >> 5)) * v.Nr + m0 + (e & 31)] = from_f32<T>(__builtin_nanf(""));
+    for (int i = tid; i < occ_db; i += 512) flags[i] = 1;
+  }
   if (occ) {
     __syncthreads();
     for (int i = tid; i < occ_db; i += 512) occ[((size_t)b * occ_db + i) * occ_sb + mt] = flags[i];

@@ -604,6 +604,40 @@ def test_screened_merge_weights_of_values_that_are_not_finite():
     assert np.array_equal(A0[0, 0][:, keep], A1[0, 0][:, keep])
 
 
+@pytest.mark.parametrize("tau", [0.1, 100.0])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_screened_merge_weights_with_destinations_that_are_not_finite(tau, value):
+    """A destination that holds a NaN or an infinity: a source's weights are NaN where its softmax is, for every
+    destination and not for the tiles near it alone, and as ever where it is not (an infinite logit of negative sign)."""
+    w = synth.scaled(W["tiny"], name="screen", dtype="bf16", B=2, H=72, W=72, C=704, tile_h=12, tile_w=12, keep=71 / 144,
+                     heads=22, tau=tau, index=45)
+    inp = synth.make_inputs(w)
+    dv = tg.Device(w, inp, 1)
+    dv.select()
+    A0, _, _ = dv.merge()
+    idx = dv.idx.cpu().numpy().reshape(w.B, -1)
+    dv.X[0, int(idx[0, 100]), 17] = float(value)  # (the chunk that holds it is not the last one)
+    print(f"[screened weights] destination {value} tau={tau}", flush=True)
+    tb.toma_profile_enable(True)
+    try:
+        tb.toma_profile_read("weights_bounds")
+        A1, Z1, _ = dv.merge(idx=dv.idx.cpu().numpy())
+        screened, _ = tb.toma_profile_read("weights_bounds")
+    finally:
+        tb.toma_profile_enable(False)
+    assert screened == 1
+    X = tg.host(dv.X)[0]
+    with np.errstate(invalid="ignore", over="ignore"):
+        logits = X[idx[0]] @ X.T / tau                 # (destinations, sources)
+        e = np.exp(logits - logits.max(axis=0))
+        bad = np.isnan((e / e.sum(axis=0)).sum(axis=0))
+    assert bad.all() if np.isnan(value) else 0 < bad.sum() < w.N
+    assert np.isnan(A1[0, 0][:, bad]).all()
+    assert not np.isnan(A1[0, 0][:, ~bad]).any() and not np.isnan(A1[1]).any()
+    assert np.isnan(Z1[0]).all() and np.array_equal(A1[1], A0[1])
+    assert np.allclose(A1[0, 0][:, ~bad].sum(axis=0), 1.0, atol=3 * tg.TOL["bf16"])
+
+
 def _crafted_weights(rng, B, D, N, case):
     """Sparse weights [B, D, N] with the sources in the order the library stores them: one to three
     destinations per source, all inside the source's own 128-destination block, plus what the case
