@@ -424,7 +424,7 @@ size_t gram_i8_workspace_bytes(const Shape &s) { return s.n_loc <= 256 ? gram_i8
 size_t gram_i8_big_bytes(const Shape &s) { return s.n_loc > 256 ? gram_i8_bytes(s) : 0; }
 
 // S for every region of a bf16 input; ws_part: gram_i8_workspace_bytes() or gram_i8_big_bytes() bytes.  Leaves the per-token
-// norms and flags where the selection kernel's prologue (larger regions: k_big_fix) finds them (returned through the pointers).
+// norms and flags where the selection kernel's prologue (larger regions: k_gram_flagged) finds them (returned through the pointers).
 int launch_gram_i8(const Shape &s, const void *X, int32_t *S, char *ws_part, const double **nrm_out,
                    const uint8_t **flag_out, hipStream_t st) {
   const size_t rows = (size_t)s.B * s.N;

@@ -39,26 +39,26 @@ constexpr double kSimScale = 1073741824.0;
 // LDS and no barrier, two chunks ahead of the products; small independent units spread evenly over
 // the chip's SIMDs, which is what bounds this kernel.  The token norms come out of the same pass
 // (sums of squares of the values a lane holds anyway, combined across the four k-groups).
-template <typename T, int KS>
-__global__ __launch_bounds__(256) void k_gram(const T *__restrict__ X, int32_t *__restrict__ S, RegionMap map,
-                                             int N, int C, int P, int n_loc, int tiles, int units) {
+// FLAGGED: only the rows and columns of S of the tokens whose bits are set in `flag_bits` (one per token of the region).
+template <typename T, int KS, bool FLAGGED>
+__device__ __forceinline__ void gram_unit(const T *__restrict__ X, int32_t *__restrict__ S, const RegionMap &map, int N, int C,
+                                          int P, int n_loc, int tiles, int units, int bp, int unit_raw,
+                                          const uint32_t *flag_bits) {
   constexpr int EPP = 16 / (int)sizeof(T);  // elements per 16-byte packet
   constexpr int NPK = 8 / EPP;              // packets per fragment (eight channels)
-  constexpr int UPW = 4 / KS;               // units per workgroup: KS waves share one, each a slice of K
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c = lane & 15;
-  // one-dimensional grid over (region, group of UPW units), remapped so that an XCD works on whole
-  // regions: their tokens then stay in that XCD's L2
-  const int groups = (units + UPW - 1) / UPW;
-  const int work = xcd_remap(blockIdx.x, gridDim.x);
-  const int bp = work / groups;
-  const int unit_raw = (work - bp * groups) * UPW + w / KS, kh = w % KS;
-  const bool live = unit_raw < units;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c = lane & 15, kh = w % KS;
+  bool live = unit_raw < units;
   const int unit = live ? unit_raw : units - 1;
   // unit enumerates the pairs (tm <= tn) row by row
   int tm = 0, rest = unit;
   while (rest >= tiles - tm) { rest -= tiles - tm; tm++; }
   const int tn = tm + rest;
   const int b = bp / P, p = bp % P;
+  uint32_t flagged = 0;  // of the 16 row tokens, then of the 16 column tokens
+  if constexpr (FLAGGED) {
+    flagged = ((flag_bits[tm >> 1] >> (16 * (tm & 1))) & 0xffffu) | (flag_bits[tn >> 1] >> (16 * (tn & 1))) << 16;
+    live = live && flagged != 0;
+  }
   const int nchunk_all = C / 32;
   const int c_lo = nchunk_all * kh / KS, nchunk = live ? nchunk_all * (kh + 1) / KS - c_lo : 0;
   const T *Xb = X + (size_t)b * N * C + 32 * c_lo;
@@ -145,10 +145,51 @@ __global__ __launch_bounds__(256) void k_gram(const T *__restrict__ X, int32_t *
   for (int r = 0; r < 4; r++) {
     const int rl = g + 4 * r, row = 16 * tm + rl;
     const double nrow = __shfl(na, rl, 64);
+    if (FLAGGED && !(((flagged >> rl) | (flagged >> (16 + c))) & 1)) continue;
     const int32_t v = (int32_t)rint(acc[r] / (nrow * nb) * kSimScale);
     Sr[(size_t)row * n_loc + col] = v;
     if (tm != tn) Sr[(size_t)col * n_loc + row] = v;
   }
+}
+
+template <typename T, int KS>
+__global__ __launch_bounds__(256) void k_gram(const T *__restrict__ X, int32_t *__restrict__ S, RegionMap map,
+                                             int N, int C, int P, int n_loc, int tiles, int units) {
+  constexpr int UPW = 4 / KS;  // units per workgroup: KS waves share one, each a slice of K
+  // one-dimensional grid over (region, group of UPW units), remapped so that an XCD works on whole
+  // regions: their tokens then stay in that XCD's L2
+  const int groups = (units + UPW - 1) / UPW;
+  const int work = xcd_remap(blockIdx.x, gridDim.x);
+  const int bp = work / groups, w = threadIdx.x >> 6;
+  gram_unit<T, KS, false>(X, S, map, N, C, P, n_loc, tiles, units, bp, (work - bp * groups) * UPW + w / KS, nullptr);
+}
+
+// Rows and columns of S of tokens flagged 2 (toma_gram_i8.hip), over what the int8 kernel left there, in regions of more
+// than 256 tokens (up to 2048; k_greedy does it for the smaller ones).  Nearly always there are none: a workgroup looks at
+// its region's flags and ends; it takes eight units, far apart, so that there are few workgroups to launch.
+// The whole selection in four regions of 1024 tokens, two samples, 640 channels, in us: no token flagged 1011, one 1042,
+// all 814 (a wave per flagged token, all its products in turn: 1011, 2083 and 3183; double precision throughout: 1091).
+constexpr int kFlaggedUnits = 2;  // units per wave
+__global__ __launch_bounds__(256) void k_gram_flagged(const bf16_t *__restrict__ X, int32_t *__restrict__ S, RegionMap map,
+                                                      int N, int C, int P, int n_loc, int tiles, int units,
+                                                      const uint8_t *__restrict__ flag) {
+  __shared__ uint32_t flag_bits[64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int groups = (units + 4 * kFlaggedUnits - 1) / (4 * kFlaggedUnits);
+  const int work = xcd_remap(blockIdx.x, gridDim.x);
+  const int bp = work / groups, b = bp / P, p = bp % P;
+  bool any = false;
+  for (int l0 = 0; l0 < n_loc; l0 += 256) {
+    const int l = l0 + (int)threadIdx.x;
+    const bool f = l < n_loc && flag[(size_t)b * N + map.token(p, min(l, n_loc - 1))] == 2;
+    const uint64_t bits = __ballot(f);
+    if (lane < 2) flag_bits[(l0 + 64 * w) / 32 + lane] = (uint32_t)(bits >> (32 * lane));
+    any |= f;
+  }
+  if (!__syncthreads_or(any)) return;
+  for (int i = 0; i < kFlaggedUnits; i++)
+    gram_unit<bf16_t, 1, true>(X, S, map, N, C, P, n_loc, tiles, units, bp, (i * groups + work - bp * groups) * 4 + w,
+                               flag_bits);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -596,27 +637,6 @@ constexpr int kCandHeld = 8;    // candidates that may exceed one column's cover
 constexpr int kSparse = 64, kSparser = 12;
 constexpr int kBackMax = 15;    // rounds of one pick between two searches for several that fail, at most
 
-// The flagged rows (see k_greedy) of regions of more than 256 tokens, before anything reads S: a wave per token, which
-// nearly always finds no flag (launch latency: 4 us).  With it the int8 similarities serve these regions too: four of
-// 1024 tokens, two samples, 640 channels, the layer 1226 us with the fp64 kernel's 137 us of similarities and 1145 without.
-__global__ __launch_bounds__(256) void k_big_fix(int32_t *__restrict__ S, RegionMap map, int P, int n, int tokens, RowFix fix) {
-  const int z = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (z >= tokens) return;
-  const int bp = z / n, t = z - bp * n, p = bp % P;
-  const size_t tok0 = (size_t)(bp / P) * fix.N, tt = tok0 + map.token(p, t);
-  if (fix.flag[tt] != 2) return;
-  int32_t *Sr = S + (size_t)bp * n * n;
-  for (int j = 0; j < n; j++) {
-    const size_t tj = tok0 + map.token(p, j);
-    const double dot = exact_dot(fix.X + tt * fix.C, fix.X + tj * fix.C, fix.C, lane);
-    if (lane == 0) {  // (two flagged tokens write the same value twice)
-      const int32_t v = (int32_t)rint(dot / (fix.nrm[tt] * fix.nrm[tj]) * kSimScale);
-      Sr[(size_t)t * n + j] = v;
-      Sr[(size_t)j * n + t] = v;
-    }
-  }
-}
-
 // State of the selection of one large region between kernels: keys (0 = picked), coverage, picks so far.
 struct BigState { uint64_t *key; int32_t *m; uint64_t *pick; };
 
@@ -1038,9 +1058,12 @@ static int select_typed(const Shape &s, const T *X, int32_t *idx, float *gain, f
   }
   KernelTimer kt(K_GREEDY, st);
   if (s.n_loc > 256) {  // (regions too large for the register-resident kernel)
-    if (fix.flag) {
-      const int tokens = s.B * s.N;  // (every token is in one region)
-      hipLaunchKernelGGL(k_big_fix, dim3((tokens + 3) / 4), dim3(256), 0, st, S, map, s.P, s.n_loc, tokens, fix);
+    if constexpr (sizeof(T) == 2) {
+      if (fix.flag) {  // (before anything reads S)
+        const int groups = (units + 4 * kFlaggedUnits - 1) / (4 * kFlaggedUnits);
+        hipLaunchKernelGGL(k_gram_flagged, dim3(groups * s.B * s.P), dim3(256), 0, st, X, S, map, s.N, s.C, s.P, s.n_loc, tiles,
+                           units, fix.flag);
+      }
     }
     const int threads = std::min(kBigThreads, (s.n_loc + 63) / 64 * 64);
     // The first n / kBigFirst picks one launch each (the variant that records gaps: none; without room for the

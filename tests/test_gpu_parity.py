@@ -401,6 +401,54 @@ def test_select_large_regions_in_fixed_point(oracle, grid, tile, C, keep, layer_
         assert np.allclose(dv.gain.cpu().numpy().reshape(gain_ref.shape), gain_ref, rtol=1e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("tile", [(32, 32), (24, 28)])
+@pytest.mark.parametrize("every", [0, 1, 7])
+def test_select_large_regions_with_many_recomputed_rows(oracle, tile, every):
+    """Tokens with more elements far below their largest than the fixed point makes up for: one of them, every seventh and
+    all.  The picks are the oracle's, and recomputing their similarities is no more than half of the whole selection (the
+    double-precision kernel, which does it for all tokens, is an eighth)."""
+    w = synth.scaled(W["sdxl1"], name="bigflag", B=2, H=2 * tile[0], W=2 * tile[1], C=640, tile_h=tile[0], tile_w=tile[1], keep=0.5,
+                     heads=10, sigma=1.5, index=71)
+    print(f"[select large regions, recomputed rows] tile {tile} every {every}", flush=True)
+    inp = synth.make_inputs(w)
+    X = inp["X"].copy()
+    low = np.arange(1, 7) * 3e-9
+    if every:
+        X[:, ::every, 10:16] = low
+    else:
+        X[1, w.N // 2 + 5, 10:16] = low
+    inp["X"] = synth.round_to_bf16(X)
+    dv = tg.Device(w, inp, 1)
+    dv.select(gap=False)
+    idx_ref, _, _ = oracle.select(tg.oracle_desc(oracle, w, 1), _f64(inp["X"]))
+    assert np.array_equal(dv.idx.cpu().numpy().reshape(idx_ref.shape), idx_ref)
+
+    def us():
+        times = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            tb.toma_select(dv.desc, dv.X, dv.idx, None, None, dv.ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3)
+        return float(np.median(times))
+
+    flagged = us()
+    tb.toma_profile_enable(True)
+    try:
+        tb.toma_profile_read("limbs")
+        tb.toma_select(dv.desc, dv.X, dv.idx, None, None, dv.ws)
+        fixed_point, _ = tb.toma_profile_read("limbs")
+    finally:
+        tb.toma_profile_enable(False)
+    assert fixed_point == 1
+    dv.X.copy_(tg.dev(synth.make_inputs(w)["X"], w.dtype))
+    plain = us()
+    print(f"  select {flagged:.0f} us, without such tokens {plain:.0f}", flush=True)
+    assert flagged < 1.5 * plain
+
+
 def _check_stage(name, got, ref, tol):
     err = tg.max_rel(got, ref)
     ex = tg.elem_excess(got, ref, tol)
