@@ -152,16 +152,27 @@ inline bool weights_single_pass(int Nr, int Dr, int C, int batch, int elem_size)
 // (the exact products are bound by latency), and writing A and comparing 0.0022 per weight; the full product as priced
 // above.  Measured (us, full and screened): 128 x 128 grid 645 and 250; SDXL's first stage 45 and 44, a Flux block 59 and
 // 79 (long rows).
+// It pays where the softmax is sharp, which the host cannot see.  Tokens of unit variance, as layers are given them, have
+// scale |x|^2 = scale C: the merge takes 694 us by the full product and 317 screened where that is 640 (128 x 128 grid, two
+// samples, 640 channels, half kept), 705 and 594 at 213, 705 and 1351 at 160 (64 x 64 with 1280 channels: 155 and 124 at
+// 1280, 169 and 170 at 213, 173 and 307 at 160).  The line lies where tokens of a third of that norm still gain.
+constexpr float kScreenSharp = 600.0f;
+// Where they are smaller still, all tiles are walked, the last 128 of a block once and the others twice, 4.2 clocks per row
+// and K step (128 x 128 grid: the merge 1585 us instead of 1430; 64 x 64, 1280 channels, 305 and 240): not screened where
+// that loses more than screening gains (64 x 64, 1920 channels, one sample: 130 us instead of 137, but 370 instead of 185).
 inline bool screen_pays(const Shape &s) {
   const int es = 2;
-  if (!gemm_async_fits(s.Nr, s.Dr, s.C, es)) return false;
-  const int batch = s.B * s.R;
+  if (!(s.scale * s.C >= kScreenSharp) || !gemm_async_fits(s.Nr, s.Dr, s.C, es)) return false;
+  const int batch = s.B * s.R, steps = s.C * es / 128;
   double full;
   if (weights_single_pass(s.Nr, s.Dr, s.C, batch, es))
     full = 19000.0 + (double)(((long long)(s.Nr / 32) * batch + 255) / 256) * (s.C * es / 128) * s.Dr * 4.0;
   else
     full = 2.0 * plan_gemm_async(s.Nr, s.Dr, s.C, batch, es, false, false, false, 3).cost + 14000.0;
-  return full > 1.3 * (60000.0 + 1500.0 * (s.C * es / 128) + 0.0022 * batch * s.Nr * s.Dr);
+  const double sharp = 60000.0 + 1500.0 * steps + 0.0022 * batch * s.Nr * s.Dr;
+  const int chunks = (s.Dr + 2047) / 2048, rounds = ((s.Nr + 31) / 32 * batch + 255) / 256;
+  const double soft = 40000.0 + (2.0 - 1.0 / chunks) * rounds * s.Dr * steps * 4.2;
+  return full > 1.3 * sharp && full * full > sharp * soft;
 }
 
 int make_shape(const toma_desc *d, const toma_attn_desc *a, Shape *s);

@@ -394,7 +394,7 @@ __global__ __launch_bounds__(512) void k_weights_fused(const RegionView<T> v, co
 // A global merge whose tiles of 32 sources x 16 destinations were screened (toma_screen.hip; A is zero so far): the same
 // workgroup of 32 sources with the marked tiles in place of all destinations, 1 to 16 per wave as the list asks.
 // Where more than 128 are marked (a softmax that is not sharp), they are walked in chunks of 128 twice: statistics, then
-// weights.
+// weights (of the last chunk first, which is still in the registers).
 // A source whose sum is not finite (a logit that is NaN or +infinity) has no zero weights, and its other ones are NaN too.
 constexpr int kListMax = 2048;   // destination tiles (32768 destinations)
 template <typename T>
@@ -540,8 +540,10 @@ __global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, c
       statistics();
       write(0);
     } else {
-      for (int e0 = 0; e0 < na; e0 += 8 * NJ) { products(e0); statistics(); }
-      for (int e0 = 0; e0 < na; e0 += 8 * NJ) { products(e0); write(e0); }
+      const int last = (na - 1) / (8 * NJ) * (8 * NJ);
+      for (int e0 = 0; e0 <= last; e0 += 8 * NJ) { products(e0); statistics(); }
+      write(last);
+      for (int e0 = 0; e0 < last; e0 += 8 * NJ) { products(e0); write(e0); }
     }
   };
   if (na > 64) run(std::integral_constant<int, 16>{});

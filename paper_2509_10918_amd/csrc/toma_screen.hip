@@ -27,6 +27,9 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // A logit so far (in units of the logit) below a lower bound of its source's largest gives a zero weight: e^-110 is
 // below half of the smallest positive number of either type; the rest covers the fp32 rounding of the logits.
 constexpr float kScreenGap = 118.0f;
+// Sources with scale |x|^2 below this do not screen: with the bound's errors (about a fifth of |x|^2) even a destination
+// at a right angle is within the gap.  Blocks of such sources mark every tile without any product.
+constexpr float kScreenSoft = 168.0f;
 // The two error terms of the bound as one product E_s F_j: sqrt(r_s^2 + (k n_s)^2) sqrt(n_j^2 + (r_j / k)^2) bounds
 // r_s n_j + n_s r_j for any k > 0 and equals it where r / n = k, which is what 4-bit rounding gives (0.09 to 0.14).
 // The third pair of terms, n_s n_j / 4096, covers the rounding of the products that the bound stands for.
@@ -41,6 +44,14 @@ __device__ __forceinline__ void load8(float (&x)[8], const bf16_t *p) {
     x[2 * i] = __builtin_bit_cast(float, u << 16);
     x[2 * i + 1] = __builtin_bit_cast(float, u & 0xffff0000u);
   }
+}
+// Does `p` hold in all 512 threads?  One barrier (what __syncthreads_and does takes two); `slot` is used once.
+__device__ __forceinline__ bool block_all(bool p, uint32_t (&slot)[8]) {
+  const uint32_t all = __all(p);
+  if ((threadIdx.x & 63) == 0) slot[threadIdx.x >> 6] = all;
+  __syncthreads();
+  const u32x4 a = *reinterpret_cast<const u32x4 *>(&slot[0]), b = *reinterpret_cast<const u32x4 *>(&slot[4]);
+  return __builtin_amdgcn_readfirstlane((int)(a[0] & a[1] & a[2] & a[3] & b[0] & b[1] & b[2] & b[3])) != 0;
 }
 // operand of a product of 4-bit floats: 32 of them in the first four registers
 __device__ __forceinline__ i32x8 four_bit(const u32x4 &q) { return (i32x8){(int)q[0], (int)q[1], (int)q[2], (int)q[3], 0, 0, 0, 0}; }
@@ -57,6 +68,7 @@ __global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<T> v, const
   __shared__ __align__(1024) WeightsLds<T> lds;
   __shared__ float best[8][32], enorm[32], sscale[32];
   __shared__ int ids[2048];
+  __shared__ __align__(16) uint32_t all_soft[8];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blocks = (v.N + 31) / 32;
@@ -86,6 +98,7 @@ __global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<T> v, const
     __syncthreads();
   }
   // ---- rows to 4 bits, norms: 16 lanes per row, 128 channels per step (2 kb of them with the padding) ----
+  bool soft;
   {
     const int mr = 4 * w + g;  // this lane's row of the block
     const bool live = m0 + mr < v.N;
@@ -142,6 +155,7 @@ __global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<T> v, const
       });
     n2 = row16_sum_f32(n2);
     r2 = row16_sum_f32(r2);
+    soft = !live || scale * n2 < kScreenSoft;
     if (c == 0 && live) {
       constexpr float k2 = kRoundRatio * kRoundRatio, tiny = 1.0f / 4096;
       const float grow = bad ? __builtin_inff() : 1.0001f / down;  // (also covers the rounding of these few operations)
@@ -151,6 +165,11 @@ __global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<T> v, const
       sscale[mr] = bad ? __builtin_nanf("") : 1.0f / down;
       dst[(size_t)b * v.N + t] = make_float2(sqrtf(n2 + r2 / k2 + tiny * n2) * grow, 1.0f / down);
     }
+  }
+
+  if (block_all(soft, all_soft)) {
+    if (tid < 32 && m0 + tid < v.N) src[(size_t)b * v.N + v.token(0, m0 + tid)] = make_float2(enorm[tid], __builtin_nanf(""));
+    return;
   }
 
   // ---- lower bound of each source's largest product: the destinations of its own region ----
@@ -217,6 +236,7 @@ __global__ __launch_bounds__(512) void k_screen(const RegionView<T> v, const int
   __shared__ __align__(16) float fj[1024], ij[1024];  // the chunk's destinations: at most eight times 128
   __shared__ int off[1024];
   __shared__ uint32_t marks[SG][8];              // [sources][128 destinations]
+  __shared__ __align__(16) uint32_t all_soft[8];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, c = lane & 15;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int work = xcd_remap(blockIdx.x, gridDim.x);
@@ -252,7 +272,15 @@ __global__ __launch_bounds__(512) void k_screen(const RegionView<T> v, const int
     ij[j] = e.y;
   }
   wait_vmcnt<0>();
-  __syncthreads();
+  // (no source here screens anything: every tile is marked, and whoever computes them writes all of A)
+  if (block_all(ts[0] != ts[0] && ts[1] != ts[1], all_soft)) {
+    if (tid < SG * octets) {
+      const int r = tid / octets, o = tid - r * octets, n = min((j1 - j0 - 128 * o + 15) / 16, 8);
+      if (m0 + 32 * r < N && n > 0)
+        act[((size_t)b * ((N + 31) / 32) + m0 / 32 + r) * act_row + ck * octets + o] = (uint8_t)((1 << n) - 1);
+    }
+    return;
+  }
   auto issue = [&](int st) {
     for (int p = w; p < pieces; p += 8) {  // piece: tile p / kc, channels 128 (p % kc) .. + 127
       const int tile = p / kc, k = p - tile * kc;

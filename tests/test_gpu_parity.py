@@ -585,16 +585,24 @@ def test_merge_unmerge_skip_only_empty_blocks(oracle, dtype, tau, C, passes):
     ("bf16", (64, 80), (16, 16), 192, 256, 0.1, ""),         # D = 3840: whole tiles of 16 destinations
     ("bf16", (72, 72), (12, 12), 71, 704, 0.1, ""),          # blocks of 32 sources in two regions, D = 2556: a ragged last tile
     ("bf16", (64, 80), (16, 16), 192, 320, 0.1, ""),
-    ("bf16", (64, 80), (16, 16), 192, 256, 100.0, ""),       # no tile is empty: more than 128 per block, in chunks, twice
-    ("bf16", (64, 80), (16, 16), 192, 320, 3.0, ""),         # some are
+    ("bf16", (64, 80), (16, 16), 192, 256, 100.0, ""),       # (soft by its descriptor: not screened)
+    ("bf16", (64, 80), (16, 16), 192, 320, 3.0, ""),
+    ("bf16", (64, 80), (16, 16), 192, 256, 0.1, "small"),    # no tile is empty: more than 128 per block, in chunks, twice
+    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "small"),     # the last chunk of 32 tiles, the last one ragged
+    ("bf16", (64, 80), (16, 16), 192, 320, 0.1, "quarter"),  # some are
+    ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "mixed"),     # blocks that screen nothing beside others
     ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "repeated"),  # destinations that repeat and lie outside their region
     ("bf16", (72, 72), (12, 12), 71, 704, 0.1, "uneven")])   # zero, tiny and large tokens
 def test_screened_merge_weights(oracle, dtype, grid, tile, d_loc, C, tau, how):
-    """Weights of large global merges, whose tiles are screened by a 4-bit product first: A / Z, Z and merged tokens
-    against the oracle, and the block map by way of the unmerge."""
+    """Weights of large global merges, whose tiles are screened by a 4-bit product first where tokens of unit variance
+    make a sharp softmax: A / Z, Z and merged tokens against the oracle, and the block map by way of the unmerge."""
+    _check_screened_weights(oracle, dtype, 2, grid, tile, d_loc, C, tau, how)
+
+
+def _check_screened_weights(oracle, dtype, B, grid, tile, d_loc, C, tau, how):
     H, Wd = grid
     th, tw = tile
-    w = synth.scaled(W["tiny"], name="screen", dtype=dtype, B=2, H=H, W=Wd, C=C, tile_h=th, tile_w=tw, keep=d_loc / (th * tw),
+    w = synth.scaled(W["tiny"], name="screen", dtype=dtype, B=B, H=H, W=Wd, C=C, tile_h=th, tile_w=tw, keep=d_loc / (th * tw),
                      heads=C // 32, tau=tau, index=43)
     print(f"[screened weights] {dtype} grid {H}x{Wd} tile {th}x{tw} D={w.D} C={C} tau={tau} {how}", flush=True)
     inp = synth.make_inputs(w)
@@ -605,17 +613,21 @@ def test_screened_merge_weights(oracle, dtype, grid, tile, d_loc, C, tau, how):
         X[:, 5::101] *= 1e-20
         X[:, 7::103] *= 3.0
         inp["X"] = synth.quantize(w, X)
+    if how in ("small", "quarter", "mixed"):
+        X = np.array(inp["X"], dtype=np.float32)
+        X[:, :w.N // 2 if how == "mixed" else w.N] *= 0.25 if how == "quarter" else 0.05
+        inp["X"] = synth.quantize(w, X)
     X = _f64(inp["X"])
     # (a weight's exponent carries the fp32 rounding of logits of up to |x|^2 / tau: eight roundings of the largest)
     tol = max(tg.TOL[dtype], 8 * 2.0 ** -24 * (X ** 2).sum(axis=-1).max() / tau)
     d = tg.oracle_desc(oracle, w, 1)
     P = w.D // d_loc
     if how == "repeated":
-        idx = rng.integers(0, w.N, size=(2, P, d_loc)).astype(np.int32)
+        idx = rng.integers(0, w.N, size=(B, P, d_loc)).astype(np.int32)
         idx[:, :, 1::2] = idx[:, :, ::2][:, :, :d_loc // 2]
     else:  # random destinations of every region (the selection itself is tested elsewhere)
         _, _, tokens = oracle.region_map(H, Wd, th, tw)
-        idx = np.stack([np.stack([rng.permutation(tokens[p])[:d_loc] for p in range(P)]) for _ in range(2)]).astype(np.int32)
+        idx = np.stack([np.stack([rng.permutation(tokens[p])[:d_loc] for p in range(P)]) for _ in range(B)]).astype(np.int32)
     A_ref, Z_ref, _ = oracle.merge_weights(d, X, idx)
     Xm_ref = oracle.merge(d, X, A_ref, Z_ref)
     dv = tg.Device(w, inp, 1)
@@ -626,7 +638,7 @@ def test_screened_merge_weights(oracle, dtype, grid, tile, d_loc, C, tau, how):
         screened, _ = tb.toma_profile_read("weights_bounds")
     finally:
         tb.toma_profile_enable(False)
-    assert screened == 1
+    assert screened == (1 if C / tau >= 600 else 0)
     _check_stage("A~", A / np.maximum(Z, 1e-20).reshape(w.B, 1, -1, 1), A_ref / np.maximum(Z_ref, 1e-20).reshape(w.B, 1, -1, 1), tol)
     _check_stage("Z", Z, Z_ref, tol)
     _check_stage("Xm", Xm, Xm_ref, tol)
@@ -652,20 +664,21 @@ def test_screened_merge_weights_of_values_that_are_not_finite():
     assert np.array_equal(A0[0, 0][:, keep], A1[0, 0][:, keep])
 
 
-@pytest.mark.parametrize("tau", [0.1, 100.0])
+@pytest.mark.parametrize("size", [1.0, 0.02])
 @pytest.mark.parametrize("value", [np.nan, np.inf])
-def test_screened_merge_weights_with_destinations_that_are_not_finite(tau, value):
+def test_screened_merge_weights_with_destinations_that_are_not_finite(size, value):
     """A destination that holds a NaN or an infinity: a source's weights are NaN where its softmax is, for every
     destination and not for the tiles near it alone, and as ever where it is not (an infinite logit of negative sign)."""
     w = synth.scaled(W["tiny"], name="screen", dtype="bf16", B=2, H=72, W=72, C=704, tile_h=12, tile_w=12, keep=71 / 144,
-                     heads=22, tau=tau, index=45)
+                     heads=22, tau=0.1, index=45)
     inp = synth.make_inputs(w)
+    inp["X"] = synth.quantize(w, np.asarray(inp["X"], dtype=np.float32) * size)  # (small tokens: a soft softmax)
     dv = tg.Device(w, inp, 1)
     dv.select()
     A0, _, _ = dv.merge()
     idx = dv.idx.cpu().numpy().reshape(w.B, -1)
     dv.X[0, int(idx[0, 100]), 17] = float(value)  # (the chunk that holds it is not the last one)
-    print(f"[screened weights] destination {value} tau={tau}", flush=True)
+    print(f"[screened weights] destination {value} tokens times {size}", flush=True)
     tb.toma_profile_enable(True)
     try:
         tb.toma_profile_read("weights_bounds")
@@ -676,7 +689,7 @@ def test_screened_merge_weights_with_destinations_that_are_not_finite(tau, value
     assert screened == 1
     X = tg.host(dv.X)[0]
     with np.errstate(invalid="ignore", over="ignore"):
-        logits = X[idx[0]] @ X.T / tau                 # (destinations, sources)
+        logits = X[idx[0]] @ X.T / 0.1                 # (destinations, sources)
         e = np.exp(logits - logits.max(axis=0))
         bad = np.isnan((e / e.sum(axis=0)).sum(axis=0))
     assert bad.all() if np.isnan(value) else 0 < bad.sum() < w.N
