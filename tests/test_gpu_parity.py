@@ -599,6 +599,17 @@ def test_screened_merge_weights(oracle, dtype, grid, tile, d_loc, C, tau, how):
     _check_screened_weights(oracle, dtype, 2, grid, tile, d_loc, C, tau, how)
 
 
+@pytest.mark.parametrize("grid,tile,d_loc,C,how", [
+    ((72, 48), (8, 12), 66, 512, ""),       # four groups of sources per workgroup of the screen, up to 640 channels
+    ((52, 64), (4, 16), 48, 1280, ""),      # the same, up to 1280
+    ((38, 64), (2, 64), 89, 1344, ""),      # the same, more (stages of 32 rows), the last 128 channels half full
+    ((38, 64), (2, 64), 89, 1344, "mixed"),
+    ((72, 72), (12, 12), 104, 1344, "")])   # eight groups, more than 1280 channels
+def test_screened_merge_weights_of_one_sample(oracle, grid, tile, d_loc, C, how):
+    """The same for the screen's other shapes of work: few sources, wide rows."""
+    _check_screened_weights(oracle, "bf16", 1, grid, tile, d_loc, C, 0.1, how)
+
+
 def _check_screened_weights(oracle, dtype, B, grid, tile, d_loc, C, tau, how):
     H, Wd = grid
     th, tw = tile
@@ -1464,6 +1475,11 @@ def test_recomputed_weights_of_narrow_rows(oracle, grid, tile, d_loc, B, C, tau,
     ((8, 32), (8, 16), 120, 96, 1, True),   # 64 logit tiles: the most
     ((16, 8), (8, 8), 24, 160, 2, False),   # two selection regions in one merge region
     ((96, 96), (4, 4), 5, 64, 4, True),  # several rounds of workgroups, two per CU
+    ((24, 24), (12, 12), 72, 640, 2, True),  # six logit tiles per wave
+    ((16, 16), (8, 16), 80, 96, 2, True),    # five, a half step at the end
+    ((14, 32), (7, 16), 56, 352, 1, True),   # three or four, one workgroup per CU
+    ((14, 16), (7, 16), 14, 352, 2, True),   # one, the same
+    ((16, 96), (4, 12), 10, 2592, 1, True),  # 48 sources, long rows, the same
 ])
 def test_merge_of_small_regions(oracle, grid, tile, d_loc, C, B, tile_local):
     """Merge regions small enough that one kernel makes their weights and their merge: ragged tiles, steps and
