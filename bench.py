@@ -46,7 +46,7 @@ def executed_fraction(amap, desc, which, tile, esize):
     return float(act.mean())
 
 
-def kernel_work(w, R, esize, exec_frac=None, int8_gram=False):
+def kernel_work(w, R, esize, exec_frac=None, int8_gram=False, screened=False):
     """Work per launch of each kernel: name -> dict(bound, amount, [equiv, limit]).
     amount = what the kernel as built has to execute or move (flops for the matrix-core kernels, bytes
     for the streaming ones); equiv = the count of the textbook formulation where the kernel reaches the
@@ -88,7 +88,7 @@ def kernel_work(w, R, esize, exec_frac=None, int8_gram=False):
                                     limit="L2 to CU bandwidth: every 32-source workgroup streams all destination rows "
                                           "(with the products or the loads taken out the loop takes 30 / 21 of its 35 us)")),
         # screened weights: exact logits with the destinations of a source's own region, and the rows in 4 bits (the
-        # screen itself runs as weights_stats and leaves zeros in A; the exact tiles as weights_write)
+        # screen itself runs as weights_stats, the exact tiles as weights_write: below)
         "weights_bounds": dict(bound=mm, amount=2 * w.B * w.N * w.d_loc * w.C, limit="a chain of dependent loads"),
         # one kernel per small merge region: logits (repeated per slice of the channels: not counted), softmax, merge
         "local_merge": dict(bound=mm, amount=f["weights"] + f["merge"],
@@ -104,6 +104,11 @@ def kernel_work(w, R, esize, exec_frac=None, int8_gram=False):
         "split_finish": dict(bound="hbm", amount=w.B * w.D * w.C * (2 * 4 + esize)),
         "occupancy": dict(bound="hbm", amount=a_bytes),   # one read of the stored weights
     }
+    if screened:
+        # the screen leaves zeros in A and reads the rows in 4 bits; its own products are in another unit and take half as long
+        work["weights_stats"] = dict(bound="hbm", amount=a_bytes + w.B * w.N * w.C / 2, limit="the zeros of A")
+        work["weights_write"] = dict(bound=mm, amount=f["weights"] * ef.get("weights_write", 0.0), equiv=f["weights"],
+                                     limit="latency: a list of marked tiles and dependent gathers per 32 sources")
     return work
 
 
@@ -357,7 +362,18 @@ def main():
             pad_d, pad_s = (-db) % dpt, (-sb) % spt
             occ = np.pad(occ, ((0, 0), (0, pad_d), (0, pad_s)))
             exec_frac["weights_write"] = float(occ.reshape(z, (db + pad_d) // dpt, dpt, (sb + pad_s) // spt, spt).any(axis=(2, 4)).mean())
-    work = kernel_work(w, R, esize, exec_frac, int8_gram="limbs" in per_kernel)
+    screened = "weights_bounds" in per_kernel
+    if screened and w.N % 32 == 0:
+        # tiles of 32 sources x 16 destinations (in grid order inside their region) that hold a nonzero weight: a lower
+        # bound on the tiles computed
+        rank = idx.sort(dim=-1).indices + (torch.arange(w.P, device="cuda") * w.d_loc).view(1, w.P, 1)
+        share = 0.0
+        for b in range(w.B):
+            rows = (A.view(w.B, w.D, w.N // 32, 32)[b] != 0).any(dim=-1)[rank[b].reshape(-1)]
+            rows = torch.nn.functional.pad(rows, (0, 0, 0, (-w.D) % 16))
+            share += float(rows.view(-1, 16, w.N // 32).any(dim=1).float().mean()) / w.B
+        exec_frac["weights_write"] = share
+    work = kernel_work(w, R, esize, exec_frac, int8_gram="limbs" in per_kernel, screened=screened)
     # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs of this command (profiles/)
     traffic = {}
     try:
