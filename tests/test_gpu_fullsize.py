@@ -68,8 +68,8 @@ def test_full_workload_layer(oracle, name, tile_local):
 
 @pytest.mark.timeout(1500)
 def test_hires_reuse_sequence_global(oracle):
-    """The 128 x 128 grid with ONE merge region per sample (A is 537 MB: two-pass weights with the
-    empty tiles skipped, the block map of a cached A) along its reuse schedule (Sec. 4.3.2): step 0 is
+    """The 128 x 128 grid with ONE merge region per sample (A is 537 MB: weights whose
+    empty tiles a 4-bit product rules out, the block map of a cached A) along its reuse schedule (Sec. 4.3.2): step 0 is
     checked completely against the oracle's layer; steps 1 (everything cached), 2 (cached picks, new
     weights) and 5 (new picks) are checked for exact picks, Z, and Y on the tokens of four sampled
     regions per sample.  For those the oracle evaluates the attention only on the destinations that
