@@ -350,24 +350,23 @@ __global__ __launch_bounds__(256, DH * sizeof(T) < 128 ? 4 : 1) void k_attn(cons
 // softmax of tile t, so that the matrix cores work on them while the vector ALU does the maxima,
 // exponentials and packing of tile t (a wave executes in order; with one or two waves per SIMD
 // nothing else would overlap the two).
-// The number of waves per workgroup is the launch's choice (blockDim.x / 64, four to twelve), 16 QT
-// queries each: with one query tile per wave it sets how many queries a workgroup takes and with
-// that how evenly the grid fills the SIMDs (launch_attn picks it per shape).  Many waves with one
-// tile each beat few waves with two: a wave alone overlaps its matrix and vector work poorly, and
-// the ring of a 128-wide head leaves room for one workgroup per CU only.  The first four waves
-// fetch the K / V tiles (the first eight where a row is 256 bytes or more: such launches have at
-// least eight).
-template <typename T, int DH, int QT>
-__global__ __launch_bounds__(QT == 1 ? 768 : 256, QT == 1 ? (DH * sizeof(T) >= 256 ? 3 : 4) : (DH * sizeof(T) >= 256 ? 1 : 2)) void k_attn_async(
-    const T *__restrict__ Q, const T *__restrict__ Kx, const T *__restrict__ V, T *__restrict__ O, int Lq, int L, int H,
-    float scale_log2, const float *__restrict__ Zs, int D, T *__restrict__ Oe) {
+// The number of waves per workgroup is the launch's choice (blockDim.x / 64, four to twelve), 16
+// queries each: it sets how many queries a workgroup takes and with that how evenly the grid fills
+// the SIMDs (launch_attn picks it per shape).  Many waves with one tile of queries each beat few
+// waves with two: a wave alone overlaps its matrix and vector work poorly.  The first four waves
+// fetch the K / V tiles (the first eight of 64-wide heads, whose launches have at least eight).
+template <int DH>
+__global__ __launch_bounds__(768, DH >= 64 ? 3 : 4) void k_attn_async(
+    const float *__restrict__ Q, const float *__restrict__ Kx, const float *__restrict__ V, float *__restrict__ O, int Lq, int L,
+    int H, float scale_log2, const float *__restrict__ Zs, int D, float *__restrict__ Oe) {
+  typedef float T;
   constexpr int ES = (int)sizeof(T), EPP = 16 / ES;
   constexpr int PPR = DH / EPP;       // 16-byte packets per K / V row
-  constexpr int KK = DH / 32, DT = DH / 16, STAGES = 4;  // QT: query tiles (of 16) per wave
+  constexpr int KK = DH / 32, DT = DH / 16, STAGES = 4;
   constexpr int CH = PPR;             // 1 KiB chunks per 64-row tile
-  constexpr int LW = QT == 1 && DH * ES >= 256 ? 8 : 4;  // waves that fetch the K / V tiles (the first LW)
+  constexpr int LW = DH >= 64 ? 8 : 4;  // waves that fetch the K / V tiles (the first LW)
   constexpr int NI = CH / LW;         // load instructions per loading wave per tile, for K and for V
-  const int QB = (int)(blockDim.x >> 6) * 16 * QT;  // queries per workgroup
+  const int QB = (int)(blockDim.x >> 6) * 16;  // queries per workgroup
   constexpr int TILE = 64 * DH;
   __shared__ __align__(1024) T Ks[STAGES][TILE];
   __shared__ __align__(1024) T Vs[STAGES][TILE];
@@ -381,25 +380,17 @@ __global__ __launch_bounds__(QT == 1 ? 768 : 256, QT == 1 ? (DH * sizeof(T) >= 2
   const int qb = work % nq, h = (work / nq) % H, b = work / (nq * H);
   const size_t head = ((size_t)b * H + h) * L * DH;
   const T *Qh = Q + ((size_t)b * H + h) * Lq * DH, *Kh = Kx + head, *Vh = V + head;
-  const int q_w = qb * QB + w * (16 * QT);
+  const int q_w = qb * QB + w * 16;
   const int nt = (L + 63) / 64;
 
-  Frag<T> fq[QT][KK];
-#pragma unroll
-  for (int qt = 0; qt < QT; qt++) {
-    int q = q_w + 16 * qt + c;
-    q = q < Lq ? q : Lq - 1;
+  Frag<T> fq[KK];
+  {
+    const int q = min(q_w + c, Lq - 1);
 #pragma unroll
     for (int kk = 0; kk < KK; kk++) {
       const T *src = Qh + (size_t)q * DH + 32 * kk + 8 * g;
-      if constexpr (sizeof(T) == 2) {
-        Pkt pk = pkt_load(src);
-        fq[qt][kk] = __builtin_bit_cast(Frag<T>, pk);
-      } else {
-        Pkt p0 = pkt_load(src), p1 = pkt_load(src + 4);
-        struct { Pkt a, b; } two = {p0, p1};
-        fq[qt][kk] = __builtin_bit_cast(Frag<T>, two);
-      }
+      const struct { Pkt a, b; } two = {pkt_load(src), pkt_load(src + 4)};
+      fq[kk] = __builtin_bit_cast(Frag<T>, two);
     }
   }
 
@@ -443,97 +434,79 @@ __global__ __launch_bounds__(QT == 1 ? 768 : 256, QT == 1 ? (DH * sizeof(T) >= 2
     }
   };
 
-  f32x4 oacc[DT][QT];
+  f32x4 oacc[DT];
 #pragma unroll
-  for (int dt = 0; dt < DT; dt++)
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) oacc[dt][qt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float m_run[QT], l_run[QT];  // reference point (a recent maximum of the raw scores) and sum per query
+  for (int dt = 0; dt < DT; dt++) oacc[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  float m_run = -__builtin_inff(), l_run = 0.f;  // reference point (a recent maximum of the raw scores) and sum of the query
   constexpr float kSlackLog2 = 8.0f;
   const float slack = kSlackLog2 / scale_log2;  // in units of the raw scores
-#pragma unroll
-  for (int qt = 0; qt < QT; qt++) { m_run[qt] = -__builtin_inff(); l_run[qt] = 0.f; }
 
-  // transposed scores of one tile: st[kt][qt] holds keys 16 kt + 4 g + r (rows) of query c (column)
+  // transposed scores of one tile: st[kt] holds keys 16 kt + 4 g + r (rows) of query c (column)
   // All K fragments of the tile are requested before the first product (a scheduling fence keeps
   // the compiler from folding each read back in front of its use: it would wait out the LDS
   // latency once per fragment instead of once per tile).
-  // (in batches of KB k-groups: all at once where the registers allow)
-  auto scores = [&](f32x4 (&st)[4][QT], const T *kt_) {
-    constexpr int KB = (QT == 1 && KK > 2) ? 2 : KK;
+  auto scores = [&](f32x4 (&st)[4], const T *kt_) {
+    Frag<T> fk[KK][4];
 #pragma unroll
-    for (int k0 = 0; k0 < KK; k0 += KB) {
-      Frag<T> fk[KB][4];
+    for (int kk = 0; kk < KK; kk++)
 #pragma unroll
-      for (int kk = 0; kk < KB; kk++)
+      for (int kt = 0; kt < 4; kt++) frag_load_kcw_sw<PPR>(fk[kk][kt], kt_, 16 * kt + c, 32 * kk + 8 * g);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kt = 0; kt < 4; kt++) frag_load_kcw_sw<PPR>(fk[kk][kt], kt_, 16 * kt + c, 32 * (k0 + kk) + 8 * g);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int kk = 0; kk < KK; kk++)
 #pragma unroll
-      for (int kk = 0; kk < KB; kk++)
-#pragma unroll
-        for (int kt = 0; kt < 4; kt++)
-#pragma unroll
-          for (int qt = 0; qt < QT; qt++) {
-            if (k0 + kk == 0) st[kt][qt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            mma16(st[kt][qt], fk[kk][kt], fq[qt][k0 + kk]);
-          }
-      if (k0 + KB < KK) __builtin_amdgcn_sched_barrier(0);
-    }
+      for (int kt = 0; kt < 4; kt++) {
+        if (kk == 0) st[kt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        mma16(st[kt], fk[kk][kt], fq[kk]);
+      }
   };
   // online softmax of one tile's scores and O^T += V^T P^T
-  auto softmax_pv = [&](f32x4 (&st)[4][QT], const T *vt_, int key0) {
+  auto softmax_pv = [&](f32x4 (&st)[4], const T *vt_, int key0) {
     if (key0 + 64 > L) {  // only the last tile can reach past the end (uniform branch)
-#pragma unroll
-      for (int qt = 0; qt < QT; qt++)
-#pragma unroll
-        for (int kt = 0; kt < 4; kt++)
-#pragma unroll
-          for (int r = 0; r < 4; r++)
-            if (key0 + 16 * kt + 4 * g + r >= L) st[kt][qt][r] = -__builtin_inff();
-    }
-    Frag<T> fp[QT][2];
-#pragma unroll
-    for (int qt = 0; qt < QT; qt++) {
-      float mx = max3_f32(st[0][qt][0], st[0][qt][1], st[0][qt][2]);
-      mx = max3_f32(mx, st[0][qt][3], st[1][qt][0]);
-#pragma unroll
-      for (int kt = 1; kt < 4; kt++) {
-        mx = max3_f32(mx, st[kt][qt][1], st[kt][qt][2]);
-        if (kt < 3) mx = max3_f32(mx, st[kt][qt][3], st[kt + 1][qt][0]);
-        else mx = max2_f32(mx, st[kt][qt][3]);
-      }
-      mx = rows4_max_f32(mx);
-      // The reference point of the exponentials follows the running maximum lazily: it moves (and
-      // the sums so far are rescaled) only when some row's maximum has grown by more than
-      // kSlackLog2 in the exponent, i.e. almost never after the first tile.  Until then the
-      // exponentials are at most 2^kSlackLog2, and the final O / l does not depend on the
-      // reference point.
-      const bool grew = __any(mx > m_run[qt] + slack);
-      if (grew) {
-        const float m_new = fmaxf(m_run[qt], mx);
-        const float alpha = __builtin_amdgcn_exp2f((m_run[qt] - m_new) * scale_log2);
-        m_run[qt] = m_new;
-        l_run[qt] *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DT; dt++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) oacc[dt][qt][r] *= alpha;
-      }
-      const float mc = m_run[qt] * scale_log2;
-      float psum = 0.f;
 #pragma unroll
       for (int kt = 0; kt < 4; kt++)
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
-          float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][qt][r], scale_log2, -mc));
-          st[kt][qt][r] = pv;
-          psum += pv;
-        }
-      l_run[qt] += psum;
-      pack_probs(fp[qt][0], st[0][qt], st[1][qt]);
-      pack_probs(fp[qt][1], st[2][qt], st[3][qt]);
+        for (int r = 0; r < 4; r++)
+          if (key0 + 16 * kt + 4 * g + r >= L) st[kt][r] = -__builtin_inff();
     }
+    float mx = max3_f32(st[0][0], st[0][1], st[0][2]);
+    mx = max3_f32(mx, st[0][3], st[1][0]);
+#pragma unroll
+    for (int kt = 1; kt < 4; kt++) {
+      mx = max3_f32(mx, st[kt][1], st[kt][2]);
+      if (kt < 3) mx = max3_f32(mx, st[kt][3], st[kt + 1][0]);
+      else mx = max2_f32(mx, st[kt][3]);
+    }
+    mx = rows4_max_f32(mx);
+    // The reference point of the exponentials follows the running maximum lazily: it moves (and
+    // the sums so far are rescaled) only when some row's maximum has grown by more than
+    // kSlackLog2 in the exponent, i.e. almost never after the first tile.  Until then the
+    // exponentials are at most 2^kSlackLog2, and the final O / l does not depend on the
+    // reference point.
+    if (__any(mx > m_run + slack)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; dt++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) oacc[dt][r] *= alpha;
+    }
+    const float mc = m_run * scale_log2;
+    float psum = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < 4; kt++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][r], scale_log2, -mc));
+        st[kt][r] = pv;
+        psum += pv;
+      }
+    l_run += psum;
+    Frag<T> fp[2];
+    pack_probs(fp[0], st[0], st[1]);
+    pack_probs(fp[1], st[2], st[3]);
     // slot s of k-group g is key 32 u + 4 g + s (s < 4) or 32 u + 16 + 4 g + s - 4, matching how
     // the probabilities were packed
 #pragma unroll
@@ -542,8 +515,7 @@ __global__ __launch_bounds__(QT == 1 ? 768 : 256, QT == 1 ? (DH * sizeof(T) >= 2
       for (int dt = 0; dt < DT; dt++) {
         Frag<T> fv;
         frag_load_ks_sw<PPR, true>(fv, vt_, 32 * u + 4 * g, 32 * u + 16 + 4 * g, 16 * dt, lane);
-#pragma unroll
-        for (int qt = 0; qt < QT; qt++) mma16(oacc[dt][qt], fv, fp[qt][u]);
+        mma16(oacc[dt], fv, fp[u]);
       }
   };
 
@@ -555,11 +527,11 @@ __global__ __launch_bounds__(QT == 1 ? 768 : 256, QT == 1 ? (DH * sizeof(T) >= 2
   if (nt > 2) issue(2, 2);
   if (nt > 2) wait_vmcnt<4 * NI>(); else if (nt > 1) wait_vmcnt<2 * NI>(); else wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
-  f32x4 sa[4][QT], sb[4][QT];
+  f32x4 sa[4], sb[4];
   scores(sa, Ks[0]);
   // one step per 64 keys; ring position and score buffer are compile-time constants of each of
   // the four unrolled copies
-  auto tile_step = [&](auto stage_c, f32x4 (&cur)[4][QT], f32x4 (&nxt)[4][QT], int it) {
+  auto tile_step = [&](auto stage_c, f32x4 (&cur)[4], f32x4 (&nxt)[4], int it) {
     constexpr int ST = decltype(stage_c)::value;
     if (it + 1 < nt) {
       // this wave's part of tile it + 1 has landed (tile it + 2 may still be in flight); after the
@@ -580,27 +552,22 @@ __global__ __launch_bounds__(QT == 1 ? 768 : 256, QT == 1 ? (DH * sizeof(T) >= 2
   }
 
   const int Cw = H * DH;
+  // (One trip.  As straight code the same epilogue changes the register allocation of the main loop: 40 spilled registers
+  // instead of 36 for 64-wide heads, a layer of 128 tokens 64.8 us instead of 64.4.)
 #pragma unroll
-  for (int qt = 0; qt < QT; qt++) {
-    const float l = rows4_sum_f32(l_run[qt]);
-    float inv = 1.0f / l;
-    int q = q_w + 16 * qt + c;
+  for (int trip = 0; trip < 1; trip++) {
+    float inv = 1.0f / rows4_sum_f32(l_run);
+    const int q = q_w + c;
     if (q >= Lq) continue;
     if (Zs && q < D) inv /= fmaxf(Zs[(size_t)b * D + q], 1e-20f);  // unmerge input: O / Z
     // (extra-token rows straight to their own output when the caller has one)
     T *dst = (Oe && q >= D ? Oe + ((size_t)b * (Lq - D) + (q - D)) * Cw : O + ((size_t)b * Lq + q) * Cw) + h * DH + 4 * g;
 #pragma unroll
-    for (int dt = 0; dt < DT; dt++) {
-      alignas(16) T o[4];
-#pragma unroll
-      for (int r = 0; r < 4; r++) o[r] = from_f32<T>(oacc[dt][qt][r] * inv);
-      if (sizeof(T) == 2) *reinterpret_cast<u32x2 *>(dst + 16 * dt) = *reinterpret_cast<u32x2 *>(o);
-      else *reinterpret_cast<u32x4 *>(dst + 16 * dt) = *reinterpret_cast<u32x4 *>(o);
-    }
+    for (int dt = 0; dt < DT; dt++) store4<T>(dst + 16 * dt, oacc[dt] * inv);
   }
 }
 
-// Waves per workgroup for k_attn_async with one query tile per wave.  Model (fitted to sweeps of
+// Waves per workgroup for k_attn_async.  Model (fitted to sweeps of
 // the wave count over sequence lengths 512 .. 8192): workgroups are placed `cap` to a CU (LDS ring
 // and register file) in rounds over the 256 CUs; the busiest SIMD of a CU then holds
 // k = cap * ceil(nw / 4) waves (a second workgroup lands on the SIMDs like the first), and a round
@@ -642,6 +609,9 @@ static int attn_waves(int L, int heads_x_batch, int ring_bytes, int waves_per_cu
 // and 5 to 80 heads.  The larger query tile is the cheaper one per query (1.1 against 1.3 us for 64 queries of a SIMD)
 // and the coarser one: 20 heads of 2048 tokens take 33.1 us with 11 waves of 16 queries and 34.7 with four of 32, of
 // 8192 tokens 461 and 376.  128-wide heads have registers for the 32-query kernel only.
+// A round is as long as its busiest SIMD, so 5 and 7 waves of 16 queries cost what 8 do, 9 and 10 what 12 do, for fewer
+// queries: they can only win a tie, and are left out because ties were not measured with them; 6 and 11 are in for the ties
+// that were (11 waves spread 20 heads of 2048 tokens over 240 CUs).  For 128-wide heads all of 4 to 8 were measured.
 struct AttnPlan { bool narrow; int waves; };
 static AttnPlan plan_attn_pipe(int Lq, int heads_x_batch, int dh) {
   AttnPlan best{dh < 128, 4};
@@ -698,7 +668,7 @@ static void launch_attn(const Shape &s, int Lq, int Lk, const T *Q, const T *K, 
     constexpr int kRing = 4 * 2 * 64 * DH * (int)sizeof(T);
     const int nw = attn_waves(Lq, s.heads * s.B, kRing, kWide ? 12 : 16, kWide ? 8 : 4, kWide ? 2.3f : 2.0f);
     dim3 grid((Lq + 16 * nw - 1) / (16 * nw) * s.heads * s.B);
-    hipLaunchKernelGGL((k_attn_async<T, DH, 1>), grid, dim3(64 * nw), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
+    hipLaunchKernelGGL((k_attn_async<DH>), grid, dim3(64 * nw), 0, st, Q, K, V, O, Lq, Lk, s.heads, scale_log2, Zs, s.D, Oe);
   } else {
     // one query tile per wave where two would leave fewer than two workgroups per CU (narrow rows only)
     constexpr bool kNarrow = DH * sizeof(T) < 128;

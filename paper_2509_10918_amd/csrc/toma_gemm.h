@@ -317,7 +317,7 @@ template <typename T> struct SwzTile {
   // read touches, per 16 lanes, four consecutive k-rows x 32 bytes: the low bits of k spread them
   // over one 128-byte bank group; bit 3 of k (the second 16 lanes of each half wave sit eight rows
   // further) selects the other 128-byte group when a row is long enough to have one.
-  // G4: the second 16 lanes sit FOUR rows further (the attention kernel's key order).  A long row
+  // G4: the second 16 lanes sit FOUR rows further (the key order of the fp32 attention kernel).  A long row
   // again has its other 128-byte group for them; with 128-byte rows, where odd and even rows already
   // alternate between the two groups, they take the 32-byte pieces that the first 16 lanes leave free.
   template <int PPR, bool G4 = false> __device__ static __forceinline__ int ks_slot(int k, int pi) {
@@ -334,14 +334,14 @@ template <typename T> struct SwzTile {
   }
 };
 
-template <int PPR, bool G4 = false>
+template <int PPR>
 __device__ __forceinline__ void frag_load_ks_sw(Frag<bf16_t> &f, const bf16_t *tile, int ka, int kb, int nb, int lane) {
   typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
   typedef short s16x8 __attribute__((ext_vector_type(8)));
   const int j = lane & 15, col = nb + 4 * (j & 3);
   const int ra = ka + (j >> 2), rb = kb + (j >> 2);
-  const bf16_t *pa = tile + SwzTile<bf16_t>::ks<PPR, G4>(ra, col >> 3) + (col & 7);
-  const bf16_t *pb = tile + SwzTile<bf16_t>::ks<PPR, G4>(rb, col >> 3) + (col & 7);
+  const bf16_t *pa = tile + SwzTile<bf16_t>::ks<PPR>(ra, col >> 3) + (col & 7);
+  const bf16_t *pb = tile + SwzTile<bf16_t>::ks<PPR>(rb, col >> 3) + (col & 7);
   s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(pa));
   s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(pb));
   s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -368,9 +368,6 @@ __device__ __forceinline__ void frag_load_kc_sw(Frag<float> &f, const float *til
 }
 
 // eight consecutive k starting at element kf of a row of PPR packets
-template <int PPR> __device__ __forceinline__ void frag_load_kcw_sw(Frag<bf16_t> &f, const bf16_t *tile, int row, int kf) {
-  f.v = *reinterpret_cast<const bf16x8 *>(tile + SwzTile<bf16_t>::kcw<PPR>(row, kf >> 3));
-}
 template <int PPR> __device__ __forceinline__ void frag_load_kcw_sw(Frag<float> &f, const float *tile, int row, int kf) {
   f32x4 a = *reinterpret_cast<const f32x4 *>(tile + SwzTile<float>::kcw<PPR>(row, kf >> 2));
   f32x4 b = *reinterpret_cast<const f32x4 *>(tile + SwzTile<float>::kcw<PPR>(row, (kf >> 2) + 1));

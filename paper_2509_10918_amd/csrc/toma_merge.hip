@@ -397,10 +397,10 @@ __global__ __launch_bounds__(512) void k_weights_fused(const RegionView<T> v, co
 // weights (of the last chunk first, which is still in the registers).
 // A source whose sum is not finite (a logit that is NaN or +infinity) has no zero weights, and its other ones are NaN too.
 constexpr int kListMax = 2048;   // destination tiles (32768 destinations)
-template <typename T>
-__global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, const int2 *__restrict__ order, float scale,
-                                                      T *__restrict__ A, const uint8_t *__restrict__ act, int act_row,
+__global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<bf16_t> v, const int2 *__restrict__ order, float scale,
+                                                      bf16_t *__restrict__ A, const uint8_t *__restrict__ act, int act_row,
                                                       uint8_t *__restrict__ occ, int occ_db, int occ_sb, int tiles) {
+  typedef bf16_t T;
   __shared__ __align__(1024) WeightsLds<T> lds;
   __shared__ float red[2][8][32];
   __shared__ float row_max[32], row_sum[32];
@@ -518,21 +518,15 @@ __global__ __launch_bounds__(512) void k_weights_sparse(const RegionView<T> v, c
           }
         if (nonzero && n < v.Dr) flags[n >> 7] = 1;  // (128 destinations; all write the same)
         T *row = A + ((size_t)b * v.Dr + n) * v.Nr + m0;
-        if constexpr (sizeof(T) == 2) {
-          // (lanes g and g ^ 1 trade halves, as in the one-pass kernel: one 16-byte packet each)
-          const u32x2 own0 = *reinterpret_cast<u32x2 *>(o[0]), own1 = *reinterpret_cast<u32x2 *>(o[1]);
-          const bool odd = g & 1;
-          const u32x2 give = odd ? own0 : own1;
-          u32x2 got;
-          got[0] = (uint32_t)__shfl_xor((int)give[0], 16, 64);
-          got[1] = (uint32_t)__shfl_xor((int)give[1], 16, 64);
-          const u32x4 pk = odd ? (u32x4){got[0], got[1], own1[0], own1[1]} : (u32x4){own0[0], own0[1], got[0], got[1]};
-          if (n < v.Dr && (!odd || m0 + 16 < v.Nr)) *reinterpret_cast<u32x4 *>(row + (odd ? 16 + 4 * (g - 1) : 4 * g)) = pk;
-        } else {
-#pragma unroll
-          for (int i = 0; i < 2; i++)
-            if (n < v.Dr && m0 + 16 * i < v.Nr) *reinterpret_cast<u32x4 *>(row + 16 * i + 4 * g) = *reinterpret_cast<u32x4 *>(o[i]);
-        }
+        // (lanes g and g ^ 1 trade halves, as in the one-pass kernel: one 16-byte packet each)
+        const u32x2 own0 = *reinterpret_cast<u32x2 *>(o[0]), own1 = *reinterpret_cast<u32x2 *>(o[1]);
+        const bool odd = g & 1;
+        const u32x2 give = odd ? own0 : own1;
+        u32x2 got;
+        got[0] = (uint32_t)__shfl_xor((int)give[0], 16, 64);
+        got[1] = (uint32_t)__shfl_xor((int)give[1], 16, 64);
+        const u32x4 pk = odd ? (u32x4){got[0], got[1], own1[0], own1[1]} : (u32x4){own0[0], own0[1], got[0], got[1]};
+        if (n < v.Dr && (!odd || m0 + 16 < v.Nr)) *reinterpret_cast<u32x4 *>(row + (odd ? 16 + 4 * (g - 1) : 4 * g)) = pk;
       }
     };
     if (na <= 8 * NJ) {
@@ -811,7 +805,7 @@ static int weights_typed(const Shape &s, const void *X, const int32_t *idx, void
       const int2 *order = reinterpret_cast<const int2 *>(ws + screen.order);
       const uint8_t *act = reinterpret_cast<const uint8_t *>(ws + screen.act);
       uint8_t *occ = w.occ_sb ? occ_out : nullptr;
-      hipLaunchKernelGGL((k_weights_sparse<T>), dim3(tiles * s.B), dim3(512), 0, st, v, order, s.scale, static_cast<T *>(A), act,
+      hipLaunchKernelGGL(k_weights_sparse, dim3(tiles * s.B), dim3(512), 0, st, v, order, s.scale, static_cast<T *>(A), act,
                          screen.act_row, occ, w.occ_db, w.occ_sb, tiles);
       return launch_status();
     }

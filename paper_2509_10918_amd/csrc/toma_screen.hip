@@ -60,11 +60,11 @@ __device__ __forceinline__ i32x8 four_bit(const u32x4 &q) { return (i32x8){(int)
 // indices, then the rows of the products, three K steps ahead).
 // q4: rows of kb bytes (64 per 128 channels, the rest of the last 128 zeros), in grid order of the tokens;
 // src, dst: per token (grid order) the two numbers k_screen needs of it as a source and as a destination.
-template <typename T>
-__global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<T> v, const int32_t *__restrict__ idx, float scale,
+__global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<bf16_t> v, const int32_t *__restrict__ idx, float scale,
                                                     int n_loc, int d_loc, uint8_t *__restrict__ q4, int kb,
                                                     float2 *__restrict__ src, float2 *__restrict__ dst,
                                                     int2 *__restrict__ order) {
+  typedef bf16_t T;
   __shared__ __align__(1024) WeightsLds<T> lds;
   __shared__ float best[8][32], enorm[32], sscale[32];
   __shared__ int ids[2048];
@@ -224,10 +224,10 @@ __global__ __launch_bounds__(512) void k_fp4_bounds(const RegionView<T> v, const
 //     s_s s_j <q_s, q_j> + E_s F_j < T_s      becomes      <q_s, q_j> + e_s f_j - t_s i_j < 0.
 // act: one byte per (sample, block of 32 sources, 128 destinations).
 // What bounds it: the zeros of A (128 x 128 grid: 537 MB, about 110 us); its own products take about half of that.
-template <typename T, int KC, int SD, int SG>
-__global__ __launch_bounds__(512) void k_screen(const RegionView<T> v, const int2 *__restrict__ order,
+template <int KC, int SD, int SG>
+__global__ __launch_bounds__(512) void k_screen(const RegionView<bf16_t> v, const int2 *__restrict__ order,
                                                 const uint8_t *__restrict__ q4, int kc, const float2 *__restrict__ src,
-                                                const float2 *__restrict__ dst, T *__restrict__ A, uint8_t *__restrict__ act,
+                                                const float2 *__restrict__ dst, bf16_t *__restrict__ A, uint8_t *__restrict__ act,
                                                 int act_row, int octets, int chunks, int tiles) {
   constexpr int NTS = SD / 16, DG = 8 / SG;  // destination tiles per stage, shares of them
   constexpr int TPW = NTS / DG, TU = TPW < 2 ? 1 : 2;  // tiles of a wave per stage, at a time
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(512) void k_screen(const RegionView<T> v, const int
   if (tid < SG * 8) marks[tid >> 3][tid & 7] = 0;
   // Zeros for this block of A, a stage's rows per stage: after its loads, so that the wait below (memory operations
   // count down in order) leaves them in flight.
-  constexpr int EPC = 16 / (int)sizeof(T), CPR = MS / EPC, ZS = SD * CPR / 512;  // packets per row, stores per thread
+  constexpr int EPC = 8, CPR = MS / EPC, ZS = SD * CPR / 512;  // packets per row, stores per thread
   const u32x4 zero = {0u, 0u, 0u, 0u};
   const int zm = min(m0 + (tid % CPR) * EPC, N - EPC), zr = tid / CPR;  // (past the end: the last packet again)
   issue(0);
@@ -350,8 +350,8 @@ __global__ __launch_bounds__(512) void k_screen(const RegionView<T> v, const int
 
 ScreenPlan plan_screen(const Shape &s, const Workspace &w) {
   ScreenPlan p{};
-  // bf16 only: the exact kernel's fp32 weights differ from the full product's in the last place of a log-sum-exp of some
-  // thousands, up to 1e-4 of a weight, and weights kept for later calls have to be the same whichever kernel made them.
+  // bf16 only: the full product's write pass subtracts a log-sum-exp rounded to fp32, in the last place of some thousands, so
+  // that exact fp32 weights differ from its by up to 1e-4: more than fp32 layers with kept weights are held to.
   // (a merge region of one selection region has no far destinations; rows of a multiple of 128 bytes and at most 3072
   // channels are what the kernels take, and a list of marked tiles has room for 32768 destinations)
   if (s.dtype != TOMA_BF16 || s.R != 1 || s.P < 4 || s.C % 64 != 0 || s.C > 3072 || s.D > 32768 || !w.z_in_merge) return p;
@@ -371,9 +371,8 @@ ScreenPlan plan_screen(const Shape &s, const Workspace &w) {
   return p;
 }
 
-template <typename T>
-static int screen_typed(const Shape &s, const ScreenPlan &p, const void *X, const int32_t *idx, void *A, char *ws, hipStream_t st) {
-  const RegionView<T> v = make_view<T>(s, X);
+int launch_screen(const Shape &s, const ScreenPlan &p, const void *X, const int32_t *idx, void *A, char *ws, hipStream_t st) {
+  const RegionView<bf16_t> v = make_view<bf16_t>(s, X);
   uint8_t *q4 = reinterpret_cast<uint8_t *>(ws + p.q4);
   int2 *order = reinterpret_cast<int2 *>(ws + p.order);
   float2 *src = reinterpret_cast<float2 *>(ws + p.src), *dst = reinterpret_cast<float2 *>(ws + p.dst);
@@ -381,7 +380,7 @@ static int screen_typed(const Shape &s, const ScreenPlan &p, const void *X, cons
   {
     KernelTimer kt(K_WBOUNDS, st);
     const dim3 grid((s.N + 31) / 32 * s.B);
-    hipLaunchKernelGGL((k_fp4_bounds<T>), grid, dim3(512), 0, st, v, idx, s.scale, s.n_loc, s.d_loc, q4, p.kc * 64, src, dst, order);
+    hipLaunchKernelGGL(k_fp4_bounds, grid, dim3(512), 0, st, v, idx, s.scale, s.n_loc, s.d_loc, q4, p.kc * 64, src, dst, order);
   }
   // 256 sources x 128 destinations per workgroup; 128 sources where that leaves CUs without one, more destinations
   // while four workgroups per CU remain
@@ -395,20 +394,16 @@ static int screen_typed(const Shape &s, const ScreenPlan &p, const void *X, cons
   KernelTimer kt(K_WSTATS, st);
 #define TOMA_SCREEN(KC, SD)                                                                                             \
   if (small)                                                                                                            \
-    hipLaunchKernelGGL((k_screen<T, KC, SD, 4>), grid, dim3(512), 0, st, v, order, q4, p.kc, src, dst, static_cast<T *>(A), \
+    hipLaunchKernelGGL((k_screen<KC, SD, 4>), grid, dim3(512), 0, st, v, order, q4, p.kc, src, dst, static_cast<bf16_t *>(A), \
                        act, p.act_row, octets, chunks, tiles);                                                          \
   else                                                                                                                  \
-    hipLaunchKernelGGL((k_screen<T, KC, SD, 8>), grid, dim3(512), 0, st, v, order, q4, p.kc, src, dst, static_cast<T *>(A), \
+    hipLaunchKernelGGL((k_screen<KC, SD, 8>), grid, dim3(512), 0, st, v, order, q4, p.kc, src, dst, static_cast<bf16_t *>(A), \
                        act, p.act_row, octets, chunks, tiles)
   if (p.kc <= 5) { TOMA_SCREEN(5, 64); }
   else if (p.kc <= 10) { TOMA_SCREEN(10, 64); }
   else { TOMA_SCREEN(24, 32); }
 #undef TOMA_SCREEN
   return launch_status();
-}
-
-int launch_screen(const Shape &s, const ScreenPlan &p, const void *X, const int32_t *idx, void *A, char *ws, hipStream_t st) {
-  return screen_typed<bf16_t>(s, p, X, idx, A, ws, st);
 }
 
 }  // namespace toma
