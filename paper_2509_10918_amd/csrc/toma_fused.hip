@@ -289,7 +289,8 @@ __global__ __launch_bounds__(512) void k_fused(const FusedPol<T, UNMERGE> pol) {
   }
 }
 
-// The same for bf16 rows of up to 640 channels, whose 32 keys fit a slot of LDS whole: every row of a tile is read from
+// The same for bf16 rows of up to 640 channels (three slots of 32 such rows, which the unmerge takes, are 120 KB of LDS; the
+// merge takes two and would go further, but it and the unmerge of a layer are one route), whose 32 keys fit a slot whole: every row of a tile is read from
 // memory once, coalesced, by the load-to-LDS path, while the tile before is worked on (in k_fused the logits' operands
 // and the values of a tile are requested when they are needed, three latencies per tile: SDXL's first stage 109 us for
 // the merge and 110 for the unmerge; 39 and 37 us so, list of tiles included).

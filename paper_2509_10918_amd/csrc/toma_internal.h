@@ -87,7 +87,9 @@ inline GemmPlan plan_gemm_async(int M, int N, int K, int batch, int elem_size, b
   const int nk = K / (128 / elem_size);
   GemmPlan best{128, 128, 1, 0.0};
   double best_cost = -1.0;
-  int most = may_split ? 8 : 1;  // K split: (fp32) never more than the bf16 figures give, which the scratch was sized by
+  // K split: fp32 never more than the bf16 figures give, whose finish pass is priced from measurements (that bounds the
+  // scratch too, which is sized by this plan)
+  int most = may_split ? 8 : 1;
   for (int pass = f32 && may_split ? 0 : 1; pass < 2; pass++) {
     best_cost = -1.0;
     for (int i = 0; i < 5; i++) {
@@ -148,7 +150,7 @@ inline bool weights_single_pass(int Nr, int Dr, int C, int batch, int elem_size)
   return single <= two;
 }
 
-// Does screening the weights (toma_screen.hip) pay?  In shader clocks: its three launches about 60000, 1500 per K step
+// Does screening the weights (toma_screen.hip, bf16) pay?  In shader clocks: its three launches about 60000, 1500 per K step
 // (the exact products are bound by latency), and writing A and comparing 0.0022 per weight; the full product as priced
 // above.  Measured (us, full and screened): 128 x 128 grid 645 and 250; SDXL's first stage 45 and 44, a Flux block 59 and
 // 79 (long rows).

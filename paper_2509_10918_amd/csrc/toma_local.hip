@@ -14,9 +14,11 @@
 // step cost a fifth of it.  Measured (us, the separate kernels and this one): regions of 64 tokens with 32 destinations,
 // width 1280, 128 regions 43.5 and 16.9; 64 with 16, 32 regions 28.8 and 13.0; 96 with 29, width 352, 45 regions 30 and 10;
 // 16 with 8, width 320, 2048 regions 96 and 26.
-// bf16 only.  fp32 gained as well (64 with 32, width 640, 48 regions 46 and 20 us), but its exact softmax differs from the
-// one by a rounded log-sum-exp, which everything else of this path stores, by up to 1e-4 of a weight: weights kept from
-// one call for the next would no longer be the same whichever size they came from.
+// bf16 only.  fp32 gained as well (64 with 32, width 640, 48 regions 46 and 20 us), but the kernels it would replace store
+// exp(logit - lse) with a log-sum-exp rounded to fp32 (WeightsPol, the write pass), up to 1e-4 of a weight away from the
+// softmax made here: fp32 weights, and layers that keep them, would have changed by more than the 1e-5 that fp32 layers with
+// kept weights are held to.  (The one-pass kernel and the recomputed weights do not round there: it is the write pass that
+// would have to change first.)
 #include <type_traits>
 
 #include "toma_gemm.h"
