@@ -710,6 +710,31 @@ def test_screened_merge_weights_with_destinations_that_are_not_finite(size, valu
     assert np.allclose(A1[0, 0][:, ~bad].sum(axis=0), 1.0, atol=3 * tg.TOL["bf16"])
 
 
+def test_screened_merge_weights_with_sources_that_are_not_finite():
+    """The same for two tokens that are no destinations, at a size that is screened: their own weights are NaN for every
+    destination, everyone else's are as they were."""
+    w = synth.scaled(W["tiny"], name="screen", dtype="bf16", B=2, H=72, W=72, C=704, tile_h=12, tile_w=12, keep=71 / 144,
+                     heads=22, tau=0.1, index=45)
+    dv = tg.Device(w, synth.make_inputs(w), 1)
+    dv.select()
+    A0, _, _ = dv.merge()
+    idx = dv.idx.cpu().numpy()
+    free = np.setdiff1d(np.arange(w.N), idx[0].reshape(-1))[[3, 400]]
+    dv.X[0, int(free[0]), 17] = float("nan")
+    dv.X[0, int(free[1]), 33] = float("inf")
+    tb.toma_profile_enable(True)
+    try:
+        tb.toma_profile_read("weights_bounds")
+        A1, _, _ = dv.merge(idx=idx)
+        screened, _ = tb.toma_profile_read("weights_bounds")
+    finally:
+        tb.toma_profile_enable(False)
+    assert screened == 1
+    keep = ~np.isin(np.arange(w.N), free)
+    assert np.isnan(A1[0, 0][:, free]).all()
+    assert np.array_equal(A0[0, 0][:, keep], A1[0, 0][:, keep]) and np.array_equal(A0[1], A1[1])
+
+
 def _crafted_weights(rng, B, D, N, case):
     """Sparse weights [B, D, N] with the sources in the order the library stores them: one to three
     destinations per source, all inside the source's own 128-destination block, plus what the case
